@@ -169,9 +169,12 @@ pearl_status run_attention(int mode, const pearl_kv_shape* s, const pearl_seq_de
     return fail(PEARL_ERR_WORKSPACE, "workspace_bytes %zu < required %zu", ws_bytes, pl.lay.total);
   hipStream_t hs = reinterpret_cast<hipStream_t>(stream);
   char* w = static_cast<char*>(ws);
-  // decode batches up to kDecPlanMaxSeqs are planned inside the attention kernel, which also
-  // merges the splits; everything else is planned by plan_kernel and merged by the merge kernels
-  const bool dec_in_kernel = mode == kModeDecode && q->batch <= kDecPlanMaxSeqs;
+  // Decode batches up to kDecPlanMaxSeqs are planned inside the attention kernel, which also merges
+  // the splits, if the batch's pages fit 32 bits and the grid holds a workgroup per kv-head;
+  // everything else is planned by plan_kernel and merged by the merge kernels.
+  const int dec_grid = mode == kModeDecode ? decode_grid(s->head_dim) : 0;
+  const bool dec_in_kernel = q->batch <= kDecPlanMaxSeqs && s->num_kv_heads <= dec_grid &&
+                             (int64_t)q->batch * cdiv(q->max_kv_len, kPage) <= INT32_MAX;
   hipError_t e = hipSuccess;
   if (k_new && !dec_in_kernel) {
     e = launch_kv_append(static_cast<const uint16_t*>(k_new), static_cast<const uint16_t*>(v_new),
@@ -213,20 +216,20 @@ pearl_status run_attention(int mode, const pearl_kv_shape* s, const pearl_seq_de
   a.tokens_per_tile = pl.p.tokens_per_tile;
   a.scale_log2 = scale * 1.4426950408889634f;
   const int64_t max_items = (pl.lay.max_pre + pl.lay.max_dec) * s->num_kv_heads;
+  DecPlanArgs d;
+  d.ctx_lens = q->ctx_lens;
+  d.batch = q->batch;
+  d.max_kv_len = q->max_kv_len;
+  d.max_dec = (int)pl.lay.max_dec;
   if (dec_in_kernel) {
-    e = launch_decode_prologue(a, q->batch, hs);
+    set_decode_runs(d, s->num_kv_heads, dec_grid);
+    e = launch_decode_prologue(a, d, hs);
     if (e != hipSuccess) return fail(PEARL_ERR_HIP, "decode prologue launch: %s", hipGetErrorString(e));
   }
   e = record_before(hs);
   if (e != hipSuccess) return fail(PEARL_ERR_HIP, "timing event: %s", hipGetErrorString(e));
   if (dec_in_kernel) {
-    DecPlanArgs d;
-    d.ctx_lens = q->ctx_lens;
-    d.batch = q->batch;
-    d.max_kv_len = q->max_kv_len;
-    d.pps_min = pl.p.pages_per_split;
-    d.max_dec = (int)pl.lay.max_dec;
-    e = launch_decode(a, d, s->head_dim, pl.lay.max_dec * s->num_kv_heads, hs);
+    e = launch_decode(a, d, s->head_dim, dec_grid, hs);
   } else {
     const int kinds = mode == kModePrefill ? 1 : (mode == kModeDecode ? 2 : 3);
     e = launch_attention(a, s->head_dim, kinds, max_items, (int)pl.lay.max_pre, hs);

@@ -29,6 +29,7 @@
 
 #include <math.h>
 
+#include <algorithm>
 #include <atomic>
 #include <type_traits>
 #include <mutex>
@@ -986,6 +987,64 @@ __device__ __forceinline__ void decode_issue(const AttnArgs& a, int phys, int p,
   }
 }
 
+// The copies of a whole page (the stage layout of decode_issue): the lanes' byte offsets in a block
+// are the same for every page, so a page costs its two block addresses and the copies themselves.
+// An instruction's immediate offset advances the source and the LDS address alike.
+template <int D> struct PageCopies {
+  using PT = PageTile<D>;
+  int k[PT::NDMA], v[PT::NDMA];
+  __device__ __forceinline__ explicit PageCopies(int lane) {
+    const int slot = lane % PT::CPR, r0 = lane / PT::CPR;
+#pragma unroll
+    for (int i = 0; i < PT::NDMA; ++i) {            // less the immediate offset, i 1024
+      const int r = i * PT::RPI + r0;
+      k[i] = r0 * PT::ROWB + ((slot ^ PT::kswz(r)) << 4);
+      v[i] = r0 * PT::ROWB + ((slot ^ PT::vswz(r)) << 4);
+    }
+  }
+  // kb, vb: the blocks (uniform); dst: the stage (uniform)
+  __device__ __forceinline__ void issue(const uint16_t* kb, const uint16_t* vb, const char* dst) const {
+    const unsigned lds = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)((LDS_AS const char*)dst));
+    unsigned saved;
+    if constexpr (D == 128) {
+      static_assert(PT::NDMA == (D == 128 ? 4 : 2) && PT::TBYTES == PT::NDMA * 1024, "page copies");
+      __asm__ volatile(
+          "s_mov_b32 %0, m0\n\t"
+          "s_mov_b32 m0, %1\n\t"
+          "s_nop 0\n\t"
+          "global_load_lds_dwordx4 %4, %2 nt\n\t"
+          "global_load_lds_dwordx4 %5, %2 offset:1024 nt\n\t"
+          "global_load_lds_dwordx4 %6, %2 offset:2048 nt\n\t"
+          "global_load_lds_dwordx4 %7, %2 offset:3072 nt\n\t"
+          "s_add_u32 m0, %1, 0x1000\n\t"
+          "s_nop 0\n\t"
+          "global_load_lds_dwordx4 %8, %3 nt\n\t"
+          "global_load_lds_dwordx4 %9, %3 offset:1024 nt\n\t"
+          "global_load_lds_dwordx4 %10, %3 offset:2048 nt\n\t"
+          "global_load_lds_dwordx4 %11, %3 offset:3072 nt\n\t"
+          "s_mov_b32 m0, %0"
+          : "=&s"(saved)
+          : "s"(lds), "s"(kb), "s"(vb), "v"(k[0]), "v"(k[1]), "v"(k[2]), "v"(k[3]), "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3])
+          : "memory", "scc");
+    } else {
+      __asm__ volatile(
+          "s_mov_b32 %0, m0\n\t"
+          "s_mov_b32 m0, %1\n\t"
+          "s_nop 0\n\t"
+          "global_load_lds_dwordx4 %4, %2 nt\n\t"
+          "global_load_lds_dwordx4 %5, %2 offset:1024 nt\n\t"
+          "s_add_u32 m0, %1, 0x800\n\t"
+          "s_nop 0\n\t"
+          "global_load_lds_dwordx4 %6, %3 nt\n\t"
+          "global_load_lds_dwordx4 %7, %3 offset:1024 nt\n\t"
+          "s_mov_b32 m0, %0"
+          : "=&s"(saved)
+          : "s"(lds), "s"(kb), "s"(vb), "v"(k[0]), "v"(k[1]), "v"(v[0]), "v"(v[1])
+          : "memory", "scc");
+    }
+  }
+};
+
 // Attends the G heads to logical page p staged at buf, updating the wave's online softmax state.
 template <int D>
 __device__ __forceinline__ void decode_consume(int p, int kv, const bf16x8* qop, f32x4* oacc, float& m_run,
@@ -1048,120 +1107,20 @@ struct DecItem {
   int b, split, g, q_row, kv, n_splits, slot_base;
 };
 
-// Split merge inside the attention kernel.  Every split of a multi-split (sequence, kv-head) pair
-// stores its partial (o~, m, l) with device-scope stores (written through to the level every XCD
-// reads) and moves on.  One item later, once every thread of the workgroup has drained its memory
-// operations (so those stores are acknowledged) and passed a barrier, one thread counts the split
-// in with a device-scope atomic in split_cnt[b][g] (zeroed before the launch); the workgroup that
-// brings the count to n_splits merges the pair (merge_in_kernel).  No release fence is issued: on
-// this chip its L2 write-back costs far more than the merge launch it replaces, and deferring the
-// count-in by one item keeps the store acknowledgements off the critical path.
-//
-// merge_in_kernel: wave w merges q-head w of the group (G <= NW) from the partials, read with
-// device-scope loads (which do not hit stale cache lines):
-//   o = sum_s 2^(m_s - m*) o~_s / sum_s 2^(m_s - m*) l_s,   lse = (m* + log2 l*) ln 2.
-// Lane s holds split s's (m, l); every lane holds D/64 dims of o.  The first block of o~ loads is
-// issued together with the (m, l) loads, so up to kMergeBlock splits cost one memory round trip.
-constexpr int kMergeBlock = 8;
-
-template <int D, int NW>
-__device__ __forceinline__ void merge_in_kernel(const AttnArgs& a, const DecItem& it) {
-  const int G = a.group, H_q = a.num_q_heads;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  if (w >= G) return;
-  constexpr int PER = D / 64;
-  constexpr int U = kMergeBlock;
-  const int hq = it.g * G + w;
-  const size_t base = (size_t)it.slot_base;
-  const int ns = it.n_splits;
-  auto ld = [](const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
-  auto o_ptr = [&](int sp) { return a.part_o + ((base + sp) * H_q + hq) * D + lane * PER; };
-  // (m, l) of the first 64 splits and o~ of the first U, all in flight together
-  float m0 = -INFINITY, l0 = 0.f;
-  if (lane < ns) {
-    m0 = ld(&a.part_ml[2 * ((base + lane) * H_q + hq)]);
-    l0 = ld(&a.part_ml[2 * ((base + lane) * H_q + hq) + 1]);
-  }
-  float v0[U][PER];
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const float* po = o_ptr(min(u, ns - 1));      // past the end: reload the last split, weight 0
-#pragma unroll
-    for (int i = 0; i < PER; ++i) v0[u][i] = ld(po + i);
-  }
-  float M = m0;
-  for (int s0 = 64; s0 < ns; s0 += 64)
-    if (s0 + lane < ns) M = fmaxf(M, ld(&a.part_ml[2 * ((base + s0 + lane) * H_q + hq)]));
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
-  float acc[PER];
-#pragma unroll
-  for (int i = 0; i < PER; ++i) acc[i] = 0.f;
-  float L = 0.f;
-  for (int s0 = 0; s0 < ns; s0 += 64) {
-    const int cnt = min(64, ns - s0);
-    float f = 0.f;
-    if (lane < cnt) {
-      const size_t pidx = (base + s0 + lane) * H_q + hq;
-      const float m = s0 == 0 ? m0 : ld(&a.part_ml[2 * pidx]);
-      const float l = s0 == 0 ? l0 : ld(&a.part_ml[2 * pidx + 1]);
-      f = fexp2(m - M);
-      L += f * l;
-    }
-    for (int j = 0; j < cnt; j += U) {
-      float v[U][PER], fj[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int jj = min(j + u, cnt - 1);
-        const float wgt = __shfl(f, jj);
-        fj[u] = j + u < cnt ? wgt : 0.f;
-        if (s0 == 0 && j == 0) {
-#pragma unroll
-          for (int i = 0; i < PER; ++i) v[u][i] = v0[u][i];
-        } else {
-          const float* po = o_ptr(s0 + jj);
-#pragma unroll
-          for (int i = 0; i < PER; ++i) v[u][i] = ld(po + i);
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int i = 0; i < PER; ++i) acc[i] += fj[u] * v[u][i];
-    }
-  }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) L += __shfl_xor(L, off);
-  const float inv = 1.0f / L;
-  uint16_t* orow = a.out + ((size_t)it.q_row * H_q + hq) * D + lane * PER;
-#pragma unroll
-  for (int i = 0; i < PER; ++i) orow[i] = bf16_bits(acc[i] * inv);
-  if (lane == 0 && a.lse) a.lse[(size_t)it.q_row * H_q + hq] = (M + flog2(L)) * kLn2;
-}
-
-// Counts a finished split in (thread 0; the caller has made its partial stores acknowledged and
-// passed a barrier); returns 1 to the thread if this was the pair's last split.
-__device__ __forceinline__ int count_split_in(const AttnArgs& a, const DecItem& it) {
-  const int prev = __hip_atomic_fetch_add(&a.split_cnt[it.b * a.num_kv_heads + it.g], 1, __ATOMIC_RELAXED,
-                                          __HIP_MEMORY_SCOPE_AGENT);
-  return prev == it.n_splits - 1;
-}
-
 // One pipeline step: issue the next page's copies into s_next (when the wave has one: `more`,
 // wave-uniform), then wait for the current page's and consume it from s_cur.  The copies are
 // issued untracked, so the compiler adds no waits of its own for them (left to itself it drained
 // every copy in flight in one of the loop's two unrolled steps); s_next was last read in the
 // previous step, whose operand reads all completed before its MFMAs.
-template <int D, bool kNew>
+template <int D>
 __device__ __forceinline__ void decode_step(const AttnArgs& a, int p_cur, int p_nxt, int phys_nxt, int g, int kv,
                                             char* __restrict__ s_next, const char* __restrict__ s_cur,
-                                            const bf16x8* qop, f32x4* oacc, float& m_run, float& l_run,
-                                            const NewRow& nr, bool more) {
+                                            const bf16x8* qop, f32x4* oacc, float& m_run, float& l_run, bool more) {
   constexpr int PAGE_LOADS = 2 * PageTile<D>::NDMA;   // vector-memory ops per page
   // the current page has landed; the copies are invisible to the compiler, so the wait is also a
   // compiler barrier that keeps the stage reads below it
   if (more) {
-    decode_issue<D, kNew>(a, phys_nxt, p_nxt, g, kv, s_next, nr);
+    decode_issue<D, false>(a, phys_nxt, p_nxt, g, kv, s_next, NewRow{-1, 0, nullptr, nullptr});
     __asm__ volatile("s_waitcnt vmcnt(%0)" ::"n"(PAGE_LOADS) : "memory");
   } else {
     __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -1169,16 +1128,11 @@ __device__ __forceinline__ void decode_step(const AttnArgs& a, int p_cur, int p_
   decode_consume<D>(p_cur, kv, qop, oacc, m_run, l_run, a.scale_log2, s_cur);
 }
 
-// kMergeHere: a multi-split (sequence, kv-head) is merged inside the attention kernel by the split
-// that finishes last (see the end of decode_split); otherwise merge_kernel runs after the launch.
-// kMergeHere: `pend` is this workgroup's previous multi-split item, not yet counted in (b < 0:
-// none); it is counted in (and merged if last) here, and becomes this item if it has splits.
-// s_flag: an LDS word.
-// before_end: called by every thread just before the item's closing barrier (decode_kernel
-// decodes its next item there, so the claim's latency hides behind this item).
-template <int D, int NW, bool kMergeHere, typename BeforeEnd>
+// One decode item of a launch planned by plan_kernel; its partials are merged by merge_kernel after
+// the launch.
+template <int D, int NW>
 __device__ __forceinline__ void decode_split(const AttnArgs& a, const DecItem& it, int pps, char* stageA,
-                                             char* stageB, DecItem& pend, int* s_flag, BeforeEnd before_end) {
+                                             char* stageB) {
   constexpr int NT = NW * 64;
   using PT = PageTile<D>;
   constexpr int MB = PT::MB;
@@ -1210,18 +1164,7 @@ __device__ __forceinline__ void decode_split(const AttnArgs& a, const DecItem& i
   // the page ids run one page ahead of the copies, which run one page ahead of the compute
   int cur = min(w, n_pg - 1);
   int ph_cur = page_id(bt_row, p_begin + cur, a.num_pages);
-  // fused append (decode kernel with k_new): the split holding the sequence's last page takes the
-  // new token's K/V from k_new / v_new; its last wave writes them into the pools once the item's
-  // reads are done (a write whose page id is out of range is skipped, as pearl_kv_append does).
-  // No other item reads that row.
-  NewRow nr{-1, 0, a.k_pool, a.v_pool};            // no new row (valid pointers, never selected)
-  if constexpr (kMergeHere) {
-    if (a.k_new && split == it.n_splits - 1) {
-      const size_t row = ((size_t)it.q_row * a.num_kv_heads + g) * D;
-      nr = NewRow{(kv - 1) / kPage, (kv - 1) % kPage, a.k_new + row, a.v_new + row};
-    }
-  }
-  if (w < n_pg) decode_issue<D, kMergeHere>(a, ph_cur, p_begin + cur, g, kv, st0, nr);
+  if (w < n_pg) decode_issue<D, false>(a, ph_cur, p_begin + cur, g, kv, st0, NewRow{-1, 0, nullptr, nullptr});
   f32x4 oacc[MB];
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb) oacc[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -1235,28 +1178,16 @@ __device__ __forceinline__ void decode_split(const AttnArgs& a, const DecItem& i
     const int pj = pi + NW;
     const int n2 = min(pj + NW, n_pg - 1);
     const int ph_n2 = page_id(bt_row, p_begin + n2, a.num_pages);
-    decode_step<D, kMergeHere>(a, p_begin + cur, p_begin + nxt, ph_nxt, g, kv, st1, st0, qop, oacc, m_run,
-                               l_run, nr, pj < n_pg);
+    decode_step<D>(a, p_begin + cur, p_begin + nxt, ph_nxt, g, kv, st1, st0, qop, oacc, m_run, l_run, pj < n_pg);
     if (pj >= n_pg) break;
     const int n3 = min(pj + 2 * NW, n_pg - 1);
     const int ph_n3 = page_id(bt_row, p_begin + n3, a.num_pages);
-    decode_step<D, kMergeHere>(a, p_begin + nxt, p_begin + n2, ph_n2, g, kv, st0, st1, qop, oacc, m_run,
-                               l_run, nr, pj + NW < n_pg);
+    decode_step<D>(a, p_begin + nxt, p_begin + n2, ph_n2, g, kv, st0, st1, qop, oacc, m_run, l_run, pj + NW < n_pg);
     cur = n2;
     nxt = n3;
     ph_nxt = ph_n3;
   }
   __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  // the new row's bytes and page id are loaded now, to be stored once the LDS merge below has
-  // waited for them
-  const bool writer = kMergeHere && nr.page >= 0 && w == NW - 1 && lane < D / 8;
-  u32x4 new_k = u32x4{0u, 0u, 0u, 0u}, new_v = new_k;
-  int new_page = -1;
-  if (writer) {
-    new_k = ld16(nr.k + 8 * lane);
-    new_v = ld16(nr.v + 8 * lane);
-    new_page = bt_row[nr.page];
-  }
   // each head's four lane groups hold different keys: sum their l
   l_run += __shfl_xor(l_run, 16);
   l_run += __shfl_xor(l_run, 32);
@@ -1275,21 +1206,6 @@ __device__ __forceinline__ void decode_split(const AttnArgs& a, const DecItem& i
   }
   __syncthreads();
   const int n_splits = it.n_splits;
-  // the previous item's partial stores: every thread drained its memory operations above
-  // (vmcnt(0)) before the barrier, so they are acknowledged.  The count-in's result is used only
-  // after the output loop, so its latency hides behind that loop.
-  int last_in = 0;
-  if constexpr (kMergeHere) {
-    // the new row's loads have completed (the barriers above waited for them); saying so here lets
-    // its stores below go out before the partial stores without any later wait reaching past them
-    __builtin_amdgcn_s_waitcnt(PEARL_VMCNT(0));
-    if (threadIdx.x == 0 && pend.b >= 0) last_in = count_split_in(a, pend);
-    if (writer && new_page >= 0 && new_page < a.num_pages) {
-      const size_t dst = (((size_t)new_page * a.num_kv_heads + g) * kPage + nr.slot) * D + 8 * lane;
-      *reinterpret_cast<u32x4*>(a.k_pool_w + dst) = new_k;
-      *reinterpret_cast<u32x4*>(a.v_pool_w + dst) = new_v;
-    }
-  }
   for (int t = threadIdx.x; t < G * D; t += NT) {
     const int head = t / D, dim = t - head * D;
     float M = -INFINITY;
@@ -1308,31 +1224,11 @@ __device__ __forceinline__ void decode_split(const AttnArgs& a, const DecItem& i
       if (dim == 0 && a.lse) a.lse[(size_t)it.q_row * H_q + hq] = (M + flog2(L)) * kLn2;
     } else {
       const size_t pidx = (size_t)(it.slot_base + split) * H_q + hq;
-      if constexpr (kMergeHere) {
-        // device-scope stores: written through to the level where every XCD reads them
-        __hip_atomic_store(&a.part_o[pidx * D + dim], o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (dim == 0) {
-          __hip_atomic_store(&a.part_ml[2 * pidx], M, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          __hip_atomic_store(&a.part_ml[2 * pidx + 1], L, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-      } else {
-        a.part_o[pidx * D + dim] = o;
-        if (dim == 0) { a.part_ml[2 * pidx] = M; a.part_ml[2 * pidx + 1] = L; }
-      }
+      a.part_o[pidx * D + dim] = o;
+      if (dim == 0) { a.part_ml[2 * pidx] = M; a.part_ml[2 * pidx + 1] = L; }
     }
   }
-  before_end();
-  if constexpr (kMergeHere) {
-    if (threadIdx.x == 0) *s_flag = last_in;
-    // the LDS scratch has been read (the next item's copies overwrite it) and s_flag written; the
-    // stores just issued stay in flight (a plain barrier, without the release fence's vmcnt(0))
-    __builtin_amdgcn_s_waitcnt(PEARL_LGKMCNT0);
-    __asm__ volatile("s_barrier" ::: "memory");
-    if (*s_flag) merge_in_kernel<D, NW>(a, pend);
-    pend = n_splits > 1 ? it : DecItem{-1, 0, 0, 0, 0, 0, 0};
-  } else {
-    __syncthreads();
-  }
+  __syncthreads();
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1436,8 +1332,7 @@ __global__ __launch_bounds__((KernelCfg<D, kKinds>::NT)) void attn_kernel(AttnAr
         const int2 en = a.entries[max_pre + (e - n_pre)];
         const SeqInfo si = a.seqinfo[en.x];
         const DecItem it{en.x, en.y, g, si.q_start, si.ctx_len + si.q_len, si.kind >> 4, a.split_base[en.x]};
-        DecItem none{-1, 0, 0, 0, 0, 0, 0};
-        decode_split<D, NW, false>(a, it, pps, stageA, stageB, none, nullptr, [] {});
+        decode_split<D, NW>(a, it, pps, stageA, stageB);
       }
     }
     __syncthreads();
@@ -1447,305 +1342,569 @@ __global__ __launch_bounds__((KernelCfg<D, kKinds>::NT)) void attn_kernel(AttnAr
 }
 
 // ------------------------------------------------------------------------------------------------
-// Decode-only batches of up to kDecPlanMaxSeqs sequences are planned inside the attention kernel:
-// every workgroup reads the lengths and builds the same work list in LDS (the same split sizing
-// and longest-first order as plan_kernel), so a decode call is one zeroing launch and this kernel,
-// with the split merge done by the last split of each (sequence, kv-head) (merge_in_kernel).
+// Decode of batches of up to kDecPlanMaxSeqs sequences: one launch of equal shares.
+//
+// The work of one kv-head is the list of the batch's pages in (sequence, page) order.  The list is
+// cut into equal shares, one per wave, so every wave streams the same number of pages whatever
+// the lengths are, and its double buffer of page copies never drains between the sequences it
+// passes through.  A workgroup holds consecutive shares of one kv-head, or the same shares of up
+// to 8 kv-heads (DecShares).
+//   * A (sequence, kv-head) pair inside one share is normalised and stored by its wave alone.
+//   * A pair cut by share boundaries leaves a partial (o~, m, l) in each wave: at most two per wave,
+//     the first pair's (kept in registers until the share ends) and the last one's.  At the end
+//     the workgroup merges those of each kv-head through LDS.
+//   * A pair cut by workgroup boundaries leaves at most two partials per workgroup and kv-head in
+//     the workspace (a first slot for the pair holding its first page, a second one for another
+//     pair), merged by the workgroup that finishes last.
+// What bounds it: the HBM read rate while it streams (decode-64 below reads 6.9 TB/s from the first
+// page to the last wave's end, the rate of a plain non-temporal read), then about 10 us of latency
+// a launch: lengths, page id and first page one after the other (3-4 us), the LDS merge, the
+// store acknowledgement, the count-in and the last merge (5-8 us).  Before, splits of equal size
+// came from a work queue and each drained its pipeline and merged 8 waves (3.6 us per split, and a
+// tail of a split's length).  Times of a call, before and now (32 q-heads, d = 128 unless said;
+// same card, in turn): 64 sequences of 2K-16K tokens, 8 kv-heads 361 -> 355 us; 256 around 6K
+// tokens, 4 kv-heads 646 -> 636; 512 of 64-1024 tokens 202 -> 195; 32 around 6K, 4 kv-heads
+// 93.3 -> 84.2; 48 of 500-6000 tokens, 16 q-heads, 8 kv-heads, d = 64 60.7 -> 55.2; one of 16000
+// tokens 34.1 -> 22.1; 200 of 40-160 tokens 37.4 -> 26.7.
+// The shares follow from the lengths alone, so results do not depend on timing.  Every workgroup
+// finds its place by itself from the prefix sums of the pages per sequence (decode_plan), so the
+// call is a zeroing launch and this kernel.
 // ------------------------------------------------------------------------------------------------
 constexpr int kDecPlanChunks = kDecPlanMaxSeqs / kThreads;
 static_assert(kDecPlanChunks * kThreads == kDecPlanMaxSeqs, "plan chunks");
 
 struct DecPlanLds {
-  int kv[kDecPlanMaxSeqs];                 // keys attended per sequence (context + the new token)
-  int full_pre[kDecPlanMaxSeqs + 1];       // exclusive prefix sums of full splits
-  int split_pre[kDecPlanMaxSeqs + 1];      // exclusive prefix sums of all splits (partial slot bases)
-  int order[kDecPlanMaxSeqs];              // sequences with a short last split, longest class first
-  int wsum[2][kWaves];
-  int cls_cnt[kDecPlanChunks][kWaves][kPartBuckets];
-  int cls_off[kDecPlanChunks][kWaves][kPartBuckets];   // first position of (chunk, wave, class) in order
-  unsigned long long pages;
-  int err, pps, n_full, n_items;
+  int pre[kDecPlanMaxSeqs + 1];            // exclusive prefix sums of pages
+  unsigned char tail[kDecPlanMaxSeqs];     // (attended keys - 1) % kPage
+  int wsum[kWaves];
+  int err;
 };
 
-// Pages per decode split over `pages` pages of H kv-heads: about kDecItemsPerCU items per compute
-// unit, a multiple of 16, at least the host's bound, at least kDecLongSplitPages while that leaves
-// 2 items per compute unit, at most kMaxPagesPerSplit (the rule plan_kernel applies).
-__device__ __forceinline__ int dec_split_pages(unsigned long long pages, int H, int pps_min) {
-  long long pps = pps_min;
-  if (pages > 0) {
-    const long long units = (long long)pages * H;
-    const long long per = (long long)kPlanComputeUnits * kDecItemsPerCU;
-    const long long want = (units + per - 1) / per;
-    const long long two = (units + 2LL * kPlanComputeUnits - 1) / (2LL * kPlanComputeUnits);
-    pps = max(pps, (want + 15) / 16 * 16);
-    pps = max(pps, min((long long)kDecLongSplitPages, (two + 15) / 16 * 16));
-    pps = min(pps, (long long)max(pps_min, kMaxPagesPerSplit));
-  }
-  return (int)pps;
+__device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
+
+// Pages and attended keys of one sequence from its length; false if it violates the host bounds.
+__device__ __forceinline__ bool dec_seq(const AttnArgs& a, const DecPlanArgs& d, int b, int& pages, int& tail) {
+  const int ctx = d.ctx_lens[b];
+  const long long kv = (long long)ctx + 1;
+  if (ctx < 0 || kv > d.max_kv_len || (kv + kPage - 1) / kPage > a.bt_stride) return false;
+  pages = (int)((kv + kPage - 1) / kPage);
+  tail = ctx % kPage;
+  return true;
 }
 
-// Validates the lengths against the host bounds (any violation: no work, error 1) and builds the
-// list; splits beyond the workspace's partial slots give no work and error 2.  Ends with a barrier.
-// Sequences are taken kThreads at a time (chunks); a batch of at most kThreads sequences runs one.
-__device__ __forceinline__ void decode_plan(const AttnArgs& a, const DecPlanArgs& d, DecPlanLds& P) {
-  constexpr int C = kDecPlanChunks;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int B = d.batch, H = a.num_kv_heads;
-  const int nch = (B + kThreads - 1) / kThreads;    // chunks holding sequences (<= C)
-  if (tid == 0) { P.pages = 0; P.err = 0; }
-  int pages[C];
-  bool bad = false;
-#pragma unroll
-  for (int c = 0; c < C; ++c) {
-    const int b = c * kThreads + tid;
-    pages[c] = 0;
-    if (b < B) {
-      const int ctx = d.ctx_lens[b];
-      const long long kv = (long long)ctx + 1;
-      if (ctx < 0 || kv > d.max_kv_len || (kv + kPage - 1) / kPage > a.bt_stride) {
-        bad = true;
-      } else {
-        pages[c] = (int)((kv + kPage - 1) / kPage);
-        P.kv[b] = (int)kv;
-      }
-    }
-  }
-  unsigned long long wsum = 0;
-#pragma unroll
-  for (int c = 0; c < C; ++c) {
-    unsigned sum = pages[c];                        // 64 sequences of < 2^21 pages
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
-    wsum += sum;
-  }
-  const bool wave_bad = __any(bad);
-  __syncthreads();                                  // P.pages and P.err are initialised
-  if (lane == 0) {
-    atomicAdd(&P.pages, wsum);
-    if (wave_bad) atomicOr(&P.err, 1);
-  }
-  __syncthreads();
-  if (tid == 0) P.pps = dec_split_pages(P.pages, H, d.pps_min);
-  __syncthreads();
-  const int pps = P.pps;
-  const int err = P.err;
-  if (err) {
-#pragma unroll
-    for (int c = 0; c < C; ++c) pages[c] = 0;
-  }
-  const float inv_pps = (float)kPartBuckets / (float)pps;
-  int cls[C], rank[C];
-#pragma unroll
-  for (int c = 0; c < C; ++c) { cls[c] = -1; rank[c] = 0; }
-  int carry_f = 0, carry_s = 0;
-#pragma unroll
-  for (int c = 0; c < C; ++c) {
-    if (c >= nch) break;                            // uniform
-    const int b = c * kThreads + tid;
-    const int nf = pages[c] / pps, rest = pages[c] - nf * pps;
-    const int ns = nf + (rest > 0);
-    cls[c] = rest > 0 ? part_bucket(rest, inv_pps) : -1;
-    int incl_f = nf, incl_s = ns;
+// Builds the prefix sums; returns the total pages, or -1 if a length violates the host bounds.
+// Batches of at most 64 sequences: every wave builds the same list (the same values to the same
+// words), a lane per sequence, so no barrier is needed.
+__device__ __forceinline__ int decode_plan(const AttnArgs& a, const DecPlanArgs& d, DecPlanLds& P) {
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, B = d.batch;
+  auto wave_scan = [&](int v) {
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
-      const int vf = __shfl_up(incl_f, off), vs = __shfl_up(incl_s, off);
-      if (lane >= off) { incl_f += vf; incl_s += vs; }
+      const int u = __shfl_up(v, off);
+      if (lane >= off) v += u;
     }
-    if (lane == 63) { P.wsum[0][wv] = incl_f; P.wsum[1][wv] = incl_s; }
-    // size classes of the short last splits: counts per (chunk, wave) and ranks inside the wave
+    return v;
+  };
+  if (B <= 64) {
+    int pages = 0, tail = 0;
+    const bool bad = lane < B && !dec_seq(a, d, lane, pages, tail);
+    const int incl = wave_scan(pages);
+    if (lane < B) {
+      P.pre[lane + 1] = incl;
+      P.tail[lane] = (unsigned char)tail;
+    }
+    if (lane == 0) P.pre[0] = 0;
+    const int total = __shfl(incl, 63);
+    return __any(bad) ? -1 : total;
+  }
+  if (tid == 0) { P.err = 0; P.pre[0] = 0; }
+  __syncthreads();
+  int carry = 0;
 #pragma unroll
-    for (int k = 0; k < kPartBuckets; ++k) {
-      const unsigned long long m = __ballot(cls[c] == k);
-      if (lane == 0) P.cls_cnt[c][wv][k] = __popcll(m);
-      if (cls[c] == k) rank[c] = __popcll(m & ((1ull << lane) - 1ull));
-    }
+  for (int c = 0; c < kDecPlanChunks; ++c) {
+    if (c * kThreads >= B) break;                   // uniform
+    const int b = c * kThreads + tid;
+    int pages = 0, tail = 0;
+    const bool bad = b < B && !dec_seq(a, d, b, pages, tail);
+    const int incl = wave_scan(pages);
+    if (lane == 63) P.wsum[wv] = incl;
+    if (__any(bad) && lane == 0) P.err = 1;
     __syncthreads();
-    int bf = carry_f, bs = carry_s, tf = 0, ts = 0;
+    int before = carry, sum = 0;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
-      if (w < wv) { bf += P.wsum[0][w]; bs += P.wsum[1][w]; }
-      tf += P.wsum[0][w];
-      ts += P.wsum[1][w];
+      if (w < wv) before += P.wsum[w];
+      sum += P.wsum[w];
     }
-    if (b < B) { P.full_pre[b] = bf + incl_f - nf; P.split_pre[b] = bs + incl_s - ns; }
-    carry_f += tf;
-    carry_s += ts;
-    if (c + 1 < nch) __syncthreads();               // wsum is reused by the next chunk
+    if (b < B) {
+      P.pre[b + 1] = before + incl;
+      P.tail[b] = (unsigned char)tail;
+    }
+    carry += sum;
+    __syncthreads();
   }
-  if (wv == 0) {
-    // positions of the short splits: classes largest first, and inside a class (chunk, wave)
-    // order.  Lane l handles class l/4 and a quarter (4 consecutive (chunk, wave) entries) of it.
-    constexpr int E = C * kWaves;                   // (chunk, wave) entries per class
-    static_assert(E % 4 == 0, "quarters");
-    const int k = lane >> 2, q = lane & 3;
-    int cnt[E / 4], part = 0;
-#pragma unroll
-    for (int j = 0; j < E / 4; ++j) {
-      const int e = q * (E / 4) + j, c = e / kWaves, w = e - c * kWaves;
-      cnt[j] = c < nch ? P.cls_cnt[c][w][k] : 0;
-      part += cnt[j];
-    }
-    int incl = part;
-#pragma unroll
-    for (int off = 1; off < 4; off <<= 1) {
-      const int v = __shfl_up(incl, off, 4);
-      if (q >= off) incl += v;
-    }
-    const int total = __shfl(incl, (lane & ~3) + 3);   // the class's short splits
-    int t = q == 0 ? total : 0, cs = t;                 // inclusive scan of class totals over lanes
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int v = __shfl_up(cs, off);
-      if (lane >= off) cs += v;
-    }
-    int run = cs - total + incl - part;                  // class start + quarter start
-#pragma unroll
-    for (int j = 0; j < E / 4; ++j) {
-      const int e = q * (E / 4) + j, c = e / kWaves, w = e - c * kWaves;
-      P.cls_off[c][w][k] = run;
-      run += cnt[j];
-    }
-  }
-  if (tid == 0) {
-    P.full_pre[B] = carry_f;
-    P.split_pre[B] = carry_s;
-    P.n_full = carry_f;
-    P.err = err ? 1 : (carry_s > d.max_dec ? 2 : 0);
-    P.n_items = P.err ? 0 : carry_s * H;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int c = 0; c < C; ++c) {
-    const int b = c * kThreads + tid;
-    if (b < B && cls[c] >= 0) P.order[P.cls_off[c][wv][cls[c]] + rank[c]] = b;
-  }
-  __syncthreads();
+  return P.err ? -1 : carry;
 }
 
-// The same plan for batches of at most 64 sequences, built by wave 0 alone with a lane per
-// sequence: wave reductions, scans and ballots replace the LDS atomics and the barriers between
-// the phases (measured: the 8-wave plan spends about 3 us after the lengths arrive; most of it in
-// barriers).  The list is identical to decode_plan's.  Ends with a barrier.
-__device__ __forceinline__ void decode_plan_small(const AttnArgs& a, const DecPlanArgs& d, DecPlanLds& P) {
-  if (threadIdx.x < 64) {
-    const int lane = threadIdx.x, B = d.batch, H = a.num_kv_heads;
-    int pages = 0;
-    bool bad = false;
-    if (lane < B) {
-      const int ctx = d.ctx_lens[lane];
-      const long long kv = (long long)ctx + 1;
-      if (ctx < 0 || kv > d.max_kv_len || (kv + kPage - 1) / kPage > a.bt_stride) {
-        bad = true;
-      } else {
-        pages = (int)((kv + kPage - 1) / kPage);
-        P.kv[lane] = (int)kv;
-      }
-    }
-    const bool err = __any(bad);
-    unsigned total = pages;                         // 64 sequences of < 2^21 pages
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) total += __shfl_xor(total, off);
-    const int pps = dec_split_pages(total, H, d.pps_min);
-    if (err) pages = 0;
-    const int nf = pages / pps, rest = pages - nf * pps;
-    const int ns = nf + (rest > 0);
-    const int cls = rest > 0 ? part_bucket(rest, (float)kPartBuckets / (float)pps) : -1;
-    int incl_f = nf, incl_s = ns;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int vf = __shfl_up(incl_f, off), vs = __shfl_up(incl_s, off);
-      if (lane >= off) { incl_f += vf; incl_s += vs; }
-    }
-    const int tot_f = __shfl(incl_f, 63), tot_s = __shfl(incl_s, 63);
-    // position of a short split: the short splits of the classes before its own (class 0, the
-    // longest, first), then those of its class in sequence order
-    int pos = 0;
-    const unsigned long long below = (1ull << lane) - 1ull;
-#pragma unroll
-    for (int k = 0; k < kPartBuckets; ++k) {
-      const unsigned long long m = __ballot(cls == k);
-      if (k < cls) pos += __popcll(m);
-      if (k == cls) pos += __popcll(m & below);
-    }
-    if (lane < B) {
-      P.full_pre[lane] = incl_f - nf;
-      P.split_pre[lane] = incl_s - ns;
-      if (cls >= 0) P.order[pos] = lane;
-    }
-    if (lane == 0) {
-      P.full_pre[B] = tot_f;
-      P.split_pre[B] = tot_s;
-      P.n_full = tot_f;
-      P.pps = pps;
-      P.err = err ? 1 : (tot_s > d.max_dec ? 2 : 0);
-      P.n_items = P.err ? 0 : tot_s * H;
-    }
+// A place in the page list: page p (of np) of sequence b, which attends to kv keys.  All members
+// are uniform across the wave.
+struct PageCursor {
+  int b, p, np, kv;
+};
+
+// The place of entry t (< pre[B]) of the list: the sequence is found by counting prefix sums with
+// ballots (64 evenly spaced probes, then the gap between two).
+__device__ __forceinline__ PageCursor locate(const DecPlanLds& P, int t, int B) {
+  const int lane = threadIdx.x & 63;
+  const int gap = (B + 63) / 64;
+  const int blk = __popcll(__ballot(lane * gap < B && P.pre[min(lane * gap, B)] <= t)) - 1;
+  int b = blk * gap;
+  if (gap > 1) {
+    const int i1 = b + 1 + lane;
+    b += __popcll(__ballot(lane < gap - 1 && i1 < B && P.pre[min(i1, B)] <= t));
   }
-  __syncthreads();
+  b = uni(b);
+  const int first = uni(P.pre[b]);
+  const int np = uni(P.pre[b + 1]) - first;
+  return PageCursor{b, t - first, np, (np - 1) * kPage + uni(P.tail[b]) + 1};
 }
 
-// Work item `item` of the in-kernel plan: entries are the full splits in sequence order, then the
-// short last splits by size class; the kv-head runs fastest.
-__device__ __forceinline__ DecItem decode_item(const DecPlanLds& P, int item, int H, int B) {
-  const int e = item / H, g = item - e * H;
-  int b, split;
-  if (e < P.n_full) {
-    int lo = 0, hi = B - 1;                         // the last sequence whose full splits start at or before e
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (P.full_pre[mid] <= e) lo = mid; else hi = mid - 1;
+// The next entry (never called on the list's last one).
+__device__ __forceinline__ void advance(const DecPlanLds& P, PageCursor& c) {
+  if (++c.p < c.np) return;
+  c.p = 0;
+  ++c.b;
+  c.np = uni(P.pre[c.b + 1]) - uni(P.pre[c.b]);
+  c.kv = (c.np - 1) * kPage + uni(P.tail[c.b]) + 1;
+}
+
+// The cut of the page list.  A workgroup takes `heads` kv-heads (a power of two up to 8 that
+// divides H) and one of n_runs runs of 8 / heads consecutive shares; the first `more` shares hold
+// len + 1 entries, the others len.  Several heads per workgroup read the adjacent blocks of a page
+// together, which HBM serves faster: 64 sequences of 2K-16K tokens take 355 us so and 363 us with
+// one head per workgroup.  But then every share's end cuts a pair between workgroups, and a pair
+// of many short shares is slow to merge: 32 sequences around 6K tokens (29 pages per share, the
+// longest pair in 36 pieces) take 104 us so and 84 us with one head.  So workgroups take several
+// heads only if a share holds at least kDecHeadPages pages (measured on both sides at 29 and 69
+// pages per share: 104 against 84 us, and 194 against 197 us).
+struct DecShares {
+  int heads, n_runs, len, more;
+  __device__ __forceinline__ DecShares(int pages, const DecPlanArgs& d) {
+    if (d.heads > 1 && pages >= kDecHeadPages * kWaves / d.heads * d.runs_heads) {
+      heads = d.heads;
+      n_runs = d.runs_heads;
+    } else {
+      heads = 1;
+      n_runs = max(1, min(d.runs_one, pages / kDecMinPages));
     }
-    b = lo;
-    split = e - P.full_pre[b];
-  } else {
-    b = P.order[e - P.n_full];
-    split = P.full_pre[b + 1] - P.full_pre[b];
+    const int n = n_runs * subs();
+    len = (int)((unsigned)pages / (unsigned)n);
+    more = pages - len * n;
   }
-  return DecItem{b, split, g, b, P.kv[b], P.split_pre[b + 1] - P.split_pre[b], P.split_pre[b]};
+  __device__ __forceinline__ int subs() const { return kWaves / heads; }   // shares per run
+  __device__ __forceinline__ int begin(int share) const { return share * len + min(share, more); }
+  __device__ __forceinline__ int run_of(int t) const {                     // the run that holds entry t
+    const int big = more * (len + 1);
+    const int share = t < big ? (unsigned)t / (unsigned)(len + 1) : more + (unsigned)(t - big) / (unsigned)max(len, 1);
+    return (unsigned)share / (unsigned)subs();
+  }
+};
+
+// A wave's partials at the end of its share, in the space of its own page stages: [0] the first
+// pair's, [1] the last one's.
+template <int D> struct ShareEnd {
+  float o[2][8][D];
+  float ml[2][8][2];
+};
+// What they are of: the sequences of the first pair (< 0: none) and the last one, whether the last
+// one started before the share, and whether the share holds pages at all.
+struct SharePairs {
+  int first_b, last_b, before, used;
+};
+// A pair cut by the workgroup's boundaries: its sequence (< 0: none), first run, runs, first slot.
+struct CutPair {
+  int b, x0, n, slot0;
+};
+
+// Two adjacent floats as one device-scope access: stores are written through to the level where
+// every XCD reads them, loads do not hit stale cache lines.
+__device__ __forceinline__ void st_dev2(float* p, float x, float y) {
+  const unsigned long long v = (unsigned long long)__builtin_bit_cast(unsigned, x) |
+                               ((unsigned long long)__builtin_bit_cast(unsigned, y) << 32);
+  __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void ld_dev2(const float* p, float& x, float& y) {
+  const unsigned long long v = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
+  x = __builtin_bit_cast(float, (unsigned)v);
+  y = __builtin_bit_cast(float, (unsigned)(v >> 32));
+}
+
+// Merge of a cut pair (kv-head g) from its partials, in the workgroup that counted itself in last:
+//   o = sum_s 2^(m_s - m*) o~_s / sum_s 2^(m_s - m*) l_s,   lse = (m* + log2 l*) ln 2.
+// A lane takes D/16 dims of a q-head and the (m, l) of that head (4 heads a pass), kMergeBlock
+// partials in flight at a time.
+constexpr int kMergeBlock = 8;
+
+template <int D>
+__device__ __forceinline__ void merge_pair(const AttnArgs& a, const CutPair& c, int g, int stride, int max_dec, int pass) {
+  constexpr int U = kMergeBlock, PER = D / 16;
+  const int G = a.group, H_q = a.num_q_heads;
+  const int ns = c.n;
+  const int lane = threadIdx.x & 63, head = 4 * pass + lane / 16, dim = lane % 16 * PER;
+  if (head >= G) return;
+  float M = -INFINITY, L = 0.f, acc[PER];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) acc[i] = 0.f;
+#pragma unroll 1
+  for (int s0 = 0; s0 < ns; s0 += U) {
+    float v[U][PER], m[U], l[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int s = min(s0 + u, ns - 1);            // past the end: the last partial, weight 0
+      const size_t slot = ((size_t)g * max_dec + (s == 0 ? c.slot0 : stride * (c.x0 + s))) * G + head;
+      ld_dev2(&a.part_ml[2 * slot], m[u], l[u]);
+#pragma unroll
+      for (int i = 0; i < PER; i += 2) ld_dev2(&a.part_o[slot * D + dim + i], v[u][i], v[u][i + 1]);
+    }
+    float M_new = M;
+#pragma unroll
+    for (int u = 0; u < U; ++u) M_new = fmaxf(M_new, m[u]);
+    const float alpha = s0 == 0 ? 0.f : fexp2(M - M_new);
+    L *= alpha;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) acc[i] *= alpha;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (s0 + u >= ns) break;
+      const float f = fexp2(m[u] - M_new);
+      L += f * l[u];
+#pragma unroll
+      for (int i = 0; i < PER; ++i) acc[i] += f * v[u][i];
+    }
+    M = M_new;
+  }
+  const float inv = 1.0f / L;
+  const size_t row = (size_t)c.b * H_q + g * G + head;
+#pragma unroll
+  for (int i = 0; i < PER; i += 4) {
+    u32x2 pk;
+    pk[0] = (uint32_t)bf16_bits(acc[i] * inv) | ((uint32_t)bf16_bits(acc[i + 1] * inv) << 16);
+    pk[1] = (uint32_t)bf16_bits(acc[i + 2] * inv) | ((uint32_t)bf16_bits(acc[i + 3] * inv) << 16);
+    *reinterpret_cast<u32x2*>(a.out + row * D + dim + i) = pk;
+  }
+  if (dim == 0 && a.lse) a.lse[row] = (M + flog2(L)) * kLn2;
 }
 
 template <int D>
-__global__ __launch_bounds__(kThreads) void decode_kernel(AttnArgs a, DecPlanArgs d) {
-  constexpr int NW = kWaves;
-  // separate objects, so the LDS reads of one are known not to alias the LDS-DMA into the other
-  __shared__ __attribute__((aligned(16))) char stageA[NW * PageTile<D>::BYTES];
-  __shared__ __attribute__((aligned(16))) char stageB[NW * PageTile<D>::BYTES];
+__global__ __launch_bounds__(kThreads, D == 64 ? 4 : 2) void decode_kernel(AttnArgs a, DecPlanArgs d) {
+  using PT = PageTile<D>;
+  constexpr int NW = kWaves, KB = PT::KB, MB = PT::MB;
+  constexpr int QB = 8 * D * 2;                     // bytes of a group's query rows (G <= 8)
+  constexpr int NQ = QB / 1024;                     // DMA instructions for them
+  constexpr int PAGE_LOADS = 2 * PT::NDMA;          // DMA instructions per page
+  __shared__ __attribute__((aligned(16))) char stage[NW * 2 * PT::BYTES];   // per wave: two pages
+  __shared__ __attribute__((aligned(16))) char qbuf[NW * QB];
   __shared__ DecPlanLds P;
-  __shared__ DecItem s_it[2];
-  __shared__ int s_flag;
-  int first = 0;
-  if (threadIdx.x == 0) first = atomicAdd(&a.ws_hdr[kHdrCounter], 1);   // in flight during the plan
-  if (d.batch <= 64) decode_plan_small(a, d, P);
-  else decode_plan(a, d, P);
-  // the error flag shares a cache line with the work counter, so it is written only when set
-  // (then no work follows); the prologue cleared it
-  if (blockIdx.x == 0 && threadIdx.x == 0 && P.err) a.ws_hdr[kHdrError] = P.err;
-  const int n_items = P.n_items, pps = P.pps, H = a.num_kv_heads, B = d.batch;
-  const DecItem none{-1, 0, 0, 0, 0, 0, 0};
-  if (threadIdx.x == 0) s_it[0] = first < n_items ? decode_item(P, first, H, B) : none;
-  __syncthreads();
-  int slot = 0;
-  DecItem pend = none;                              // previous multi-split item, not yet counted in
-  while (s_it[slot].b >= 0) {
-    const DecItem it = s_it[slot];
-    int nx = 0;
-    if (threadIdx.x == 0) nx = atomicAdd(&a.ws_hdr[kHdrCounter], 1);   // used at the item's end
-    decode_split<D, NW, true>(a, it, pps, stageA, stageB, pend, &s_flag, [&] {
-      if (threadIdx.x == 0) s_it[slot ^ 1] = nx < n_items ? decode_item(P, nx, H, B) : none;
-    });                                             // ends with a barrier
-    slot ^= 1;
+  __shared__ SharePairs ends[NW];                   // per share of the run
+  __shared__ CutPair s_cut[2];                      // of the first and the second slot
+  __shared__ int s_last[2][NW];
+  __shared__ int progress[NW];
+  static_assert(sizeof(ShareEnd<D>) <= 2 * PT::BYTES, "a wave's partials fit its stages");
+  const int lane = threadIdx.x & 63, w = uni(threadIdx.x >> 6);
+  const int gi = lane >> 4, hh = lane & 15;
+  const int G = a.group, H = a.num_kv_heads, H_q = a.num_q_heads, B = d.batch;
+  const bool head_ok = hh < G;
+
+  const int total_pages = uni(decode_plan(a, d, P));
+  if (total_pages < 0) {                            // the prologue cleared the error flag
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.ws_hdr[kHdrError] = 1;
+    return;
   }
-  if (pend.b >= 0) {                                // the last item's count-in
-    __builtin_amdgcn_s_waitcnt(PEARL_VMCNT(0));
-    __syncthreads();
-    if (threadIdx.x == 0) s_flag = count_split_in(a, pend);
-    __syncthreads();
-    if (s_flag) merge_in_kernel<D, NW>(a, pend);
+  const DecShares sh(total_pages, d);
+  const int n_blk = H / sh.heads;                   // head blocks
+  if ((int)blockIdx.x >= sh.n_runs * n_blk) return;
+  // Run x of a head block is workgroup x n_blk + (block - x) mod n_blk: the blocks of a run start
+  // together, and every XCD (workgroup mod 8) sees all of them.
+  const int x = blockIdx.x / n_blk;
+  const int g0 = (blockIdx.x + x) % n_blk * sh.heads;
+  const int sub = w / sh.heads, g = g0 + w % sh.heads;
+  const int share = x * sh.subs() + sub;
+  const int t0 = sh.begin(share), n = sh.begin(share + 1) - t0;
+  // partial slots and counters of a kv-head: two slots and a counter per run, or a slot per run,
+  // and a slot and a counter per sequence, if that is fewer
+  const bool per_pair = B < sh.n_runs;
+  const int slot_stride = per_pair ? 1 : 2;
+
+  // State of the current pair, and of the first pair if the share only holds its end.
+  f32x4 oacc[MB], o_first[MB];
+  float m_run = -INFINITY, l_run = 0.f, m_first = -INFINITY, l_first = 0.f;
+  int first_b = -1;                                 // the sequence of o_first
+  bool whole = false;                               // the current pair started inside this share
+  PageCursor cur{-1, 0, 1, 1};
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) oacc[mb] = o_first[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  char* const st = stage + w * 2 * PT::BYTES;
+  if (n > 0) {
+    char* const qb = qbuf + w * QB;
+    const ConstI32Ptr bt = (ConstI32Ptr)a.block_table;
+    auto raw_id = [&](const PageCursor& c) { return bt[(size_t)c.b * a.bt_stride + c.p]; };
+    // the group's query rows of a pair (rows past the group repeat its last one)
+    auto issue_q = [&](const PageCursor& c) {
+#pragma unroll
+      for (int i = 0; i < NQ; ++i) {
+        const int r = min((i * 64 + lane) / PT::CPR, G - 1);
+        lds_dma16_untracked(a.q + ((size_t)c.b * H_q + g * G + r) * D + (lane % PT::CPR) * 8, qb + i * 1024);
+      }
+    };
+    const PageCopies<D> copies(lane);
+    // a page's copies: a sequence's last page may hold the new row and rows past the end; every other
+    // one is two whole blocks
+    auto issue_page = [&](const PageCursor& c, int raw, char* dst) {
+      const int phys = clamp_page(raw, a.num_pages);
+      if (c.p == c.np - 1) {
+        NewRow nr{-1, 0, a.k_pool, a.v_pool};       // no new row (valid pointers, never selected)
+        if (a.k_new) {
+          const size_t row = ((size_t)c.b * H + g) * D;
+          nr = NewRow{c.p, (c.kv - 1) % kPage, a.k_new + row, a.v_new + row};
+        }
+        decode_issue<D, true>(a, phys, c.p, g, c.kv, dst, nr);
+      } else {
+        const size_t blk = ((size_t)phys * H + g) * (size_t)(kPage * D);
+        copies.issue(a.k_pool + blk, a.v_pool + blk, dst);
+      }
+    };
+    bf16x8 qop[KB];
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) qop[kb] = zero_bf16x8();
+    cur = locate(P, t0, B);
+    PageCursor nxt = cur;
+    int raw_cur = raw_id(cur), raw_nxt = 0;
+    issue_q(cur);
+    issue_page(cur, raw_cur, st);
+    if (n > 1) {
+      advance(P, nxt);
+      raw_nxt = raw_id(nxt);
+    }
+    // step k: the copies of page k + 1 go out, then page k (and its pair's query rows) is waited for
+    // and attended.  fresh: page k is the first of its pair in this share; q_sent: its query rows
+    // are on their way (they go out behind the pair's first page, a step ahead, unless the one
+    // before was itself the first page of its pair and still needs the query buffer).
+    bool fresh = true, q_sent = true;
+    int buf = 0;
+    for (int k = 0; k < n; ++k) {
+      // A SIMD's two waves (w and w ^ 4) keep pace: the one behind issues first.  Left alone, the
+      // older one always does: waves 4-7 took 17% longer than waves 0-3.
+      if (lane == 0) *(volatile int*)&progress[w] = k;
+      if (uni(*(volatile int*)&progress[w ^ 4]) > k) __builtin_amdgcn_s_setprio(1);
+      else __builtin_amdgcn_s_setprio(0);
+      // Waves of several heads go page by page together, so that the adjacent blocks of a page are
+      // read together (without this barrier the 355 us above are 362, with it every 4th page 358).
+      if (sh.heads > 1 && k < sh.len) __asm__ volatile("s_barrier" ::: "memory");
+      if (fresh && !q_sent) issue_q(cur);
+      PageCursor nn = nxt;
+      int raw_nn = 0;
+      if (k + 1 < n) {
+        const bool nxt_fresh = nxt.p == 0;
+        issue_page(nxt, raw_nxt, st + (buf ^ PT::BYTES));
+        if (k + 2 < n) {
+          advance(P, nn);
+          raw_nn = raw_id(nn);
+        }
+        q_sent = nxt_fresh && !fresh;
+        if (q_sent) {
+          issue_q(nxt);
+          __asm__ volatile("s_waitcnt vmcnt(%0)" ::"n"(PAGE_LOADS + NQ) : "memory");
+        } else {
+          __asm__ volatile("s_waitcnt vmcnt(%0)" ::"n"(PAGE_LOADS) : "memory");
+        }
+      } else {
+        __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      }
+      if (fresh) {
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) {
+          const bf16x8 q = *reinterpret_cast<const bf16x8*>(qb + (hh & 7) * (D * 2) + (4 * kb + gi) * 16);
+          qop[kb] = head_ok ? q : zero_bf16x8();
+        }
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) oacc[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        m_run = -INFINITY;
+        l_run = 0.f;
+        whole = cur.p == 0;
+      }
+      decode_consume<D>(cur.p, cur.kv, qop, oacc, m_run, l_run, a.scale_log2, st + buf);
+      const bool ends_here = cur.p == cur.np - 1;
+      if (ends_here && a.k_new) {
+        // the new token's row goes into the pools from the stage (no wave reads it from there; a
+        // page id out of range is skipped, as pearl_kv_append does)
+        const int r = (cur.kv - 1) % kPage;
+        const int c = lane % PT::CPR;
+        const bool is_v = lane >= PT::CPR;
+        const u32x4 y = *reinterpret_cast<const u32x4*>(
+            st + buf + (is_v ? PT::TBYTES + r * PT::ROWB + ((c ^ PT::vswz(r)) << 4) : PT::koff(r, c)));
+        if (lane < 2 * PT::CPR && raw_cur >= 0 && raw_cur < a.num_pages) {
+          const size_t dst = (((size_t)raw_cur * H + g) * kPage + r) * D + 8 * c;
+          *reinterpret_cast<u32x4*>((is_v ? a.v_pool_w : a.k_pool_w) + dst) = y;
+        }
+      }
+      if (ends_here) {
+        // each head's four lane groups hold different keys: sum their l
+        l_run += __shfl_xor(l_run, 16);
+        l_run += __shfl_xor(l_run, 32);
+        if (whole) {
+          if (head_ok) {
+            const size_t row = (size_t)cur.b * H_q + g * G + hh;
+            uint16_t* orow = a.out + row * D + 4 * gi;
+            const float inv = 1.0f / l_run;
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) {
+              u32x2 pk;
+              pk[0] = (uint32_t)bf16_bits(oacc[mb][0] * inv) | ((uint32_t)bf16_bits(oacc[mb][1] * inv) << 16);
+              pk[1] = (uint32_t)bf16_bits(oacc[mb][2] * inv) | ((uint32_t)bf16_bits(oacc[mb][3] * inv) << 16);
+              *reinterpret_cast<u32x2*>(orow + 16 * mb) = pk;
+            }
+            if (gi == 0 && a.lse) a.lse[row] = (m_run + flog2(l_run)) * kLn2;
+          }
+        } else {                                    // only the first pair can have started earlier
+#pragma unroll
+          for (int mb = 0; mb < MB; ++mb) o_first[mb] = oacc[mb];
+          m_first = m_run;
+          l_first = l_run;
+          first_b = cur.b;
+        }
+      }
+      fresh = ends_here;
+      if (k + 1 == n) {
+        if (ends_here) cur.b = -1;                  // the share ends with the pair's end
+        break;
+      }
+      cur = nxt;
+      raw_cur = raw_nxt;
+      nxt = nn;
+      raw_nxt = raw_nn;
+      buf ^= PT::BYTES;
+    }
+    if (cur.b >= 0) {
+      l_run += __shfl_xor(l_run, 16);
+      l_run += __shfl_xor(l_run, 32);
+    }
+  }
+
+  // the waves' partials, merged per pair through LDS
+  {
+    ShareEnd<D>& E = *reinterpret_cast<ShareEnd<D>*>(st);
+    if (head_ok) {
+      if (first_b >= 0) {
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) *reinterpret_cast<f32x4*>(&E.o[0][hh][16 * mb + 4 * gi]) = o_first[mb];
+        if (gi == 0) { E.ml[0][hh][0] = m_first; E.ml[0][hh][1] = l_first; }
+      }
+      if (cur.b >= 0) {
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) *reinterpret_cast<f32x4*>(&E.o[1][hh][16 * mb + 4 * gi]) = oacc[mb];
+        if (gi == 0) { E.ml[1][hh][0] = m_run; E.ml[1][hh][1] = l_run; }
+      }
+    }
+    if (lane == 0) ends[sub] = SharePairs{first_b, cur.b, !whole, n > 0};   // alike for all heads
+    if (threadIdx.x < 2) s_cut[threadIdx.x].b = -1;
+  }
+  // a barrier without the release fence of __syncthreads: output stores stay in flight
+  __builtin_amdgcn_s_waitcnt(PEARL_LGKMCNT0);
+  __asm__ volatile("s_barrier" ::: "memory");
+  // A pair's partials form a chain: it starts in the share the pair starts in (or in the run's first
+  // share), goes on through the last-pair partials of the following shares while the pair goes
+  // on, and closes with the first-pair partial of the share the pair ends in.  Bit q of the masks
+  // below is share q's.
+  {
+    const int subs = sh.subs();
+    const SharePairs e = ends[lane & (NW - 1)];
+    const unsigned used = (unsigned)__ballot(lane < subs && e.used);
+    const unsigned has_first = (unsigned)__ballot(lane < subs && e.first_b >= 0);
+    // bits 0..7: chains that start with share q's last pair; bit 8: the first share's first pair
+    unsigned todo = (unsigned)__ballot(lane < subs && e.last_b >= 0 && (!e.before || lane == 0)) |
+                    ((has_first & 1u) << NW);
+    const int run0 = sh.begin(x * subs);
+    const int rows = sh.heads * G;                  // q-heads of the workgroup
+    while (todo) {
+      const int q0 = __builtin_ctz(todo);
+      todo &= todo - 1;
+      const bool is_first = q0 == NW;
+      const int qb = is_first ? 0 : q0;
+      const unsigned after = is_first ? 0u : ~0u << (q0 + 1);
+      const unsigned close = has_first & after;     // its lowest bit: the share that closes the chain
+      const unsigned mid = is_first ? 0u : (used & after & ((close & -close) - 1u)) | (1u << q0);
+      const int q_close = is_first ? 0 : (close ? __builtin_ctz(close) : -1);
+      const int b = __builtin_amdgcn_readlane(is_first ? e.first_b : e.last_b, qb);
+      const bool before = is_first || __builtin_amdgcn_readlane(e.before, qb);
+      const bool cut = before || q_close < 0;       // other workgroups hold parts of it
+      const int pu = uni(P.pre[b]);                 // the pair's first entry
+      const int second = pu > run0;
+      const int slot2 = per_pair ? sh.n_runs + b : 2 * x + 1;   // the run's second slot
+      for (int t = threadIdx.x; t < rows * (D / 2); t += kThreads) {
+        const int r = t / (D / 2), dim = 2 * (t - r * (D / 2));
+        const int j = r / G, head = r - j * G;      // kv-head of the workgroup, q-head of the group
+        float M = -INFINITY, L = 0.f, o0 = 0.f, o1 = 0.f;
+        auto add = [&](int q, int which) {
+          const ShareEnd<D>& E = *reinterpret_cast<const ShareEnd<D>*>(stage + (q * sh.heads + j) * 2 * PT::BYTES);
+          const float m = E.ml[which][head][0], l = E.ml[which][head][1];
+          const float M_new = fmaxf(M, m);
+          const float fa = M == -INFINITY ? 0.f : fexp2(M - M_new), fb = fexp2(m - M_new);
+          L = fa * L + fb * l;
+          o0 = fa * o0 + fb * E.o[which][head][dim];
+          o1 = fa * o1 + fb * E.o[which][head][dim + 1];
+          M = M_new;
+        };
+        for (unsigned rest = mid; rest; rest &= rest - 1) add(__builtin_ctz(rest), 1);
+        if (q_close >= 0) add(q_close, 0);
+        if (!cut) {
+          const size_t row = (size_t)b * H_q + g0 * G + r;
+          const float inv = 1.0f / L;
+          *reinterpret_cast<uint32_t*>(a.out + row * D + dim) =
+              (uint32_t)bf16_bits(o0 * inv) | ((uint32_t)bf16_bits(o1 * inv) << 16);
+          if (dim == 0 && a.lse) a.lse[row] = (M + flog2(L)) * kLn2;
+        } else {
+          const size_t slot = ((size_t)(g0 + j) * d.max_dec + (second ? slot2 : slot_stride * x)) * G + head;
+          st_dev2(&a.part_o[slot * D + dim], o0, o1);
+          if (dim == 0) st_dev2(&a.part_ml[2 * slot], M, L);
+        }
+      }
+      if (cut && threadIdx.x == 0) {
+        const int x0 = sh.run_of(pu), x1 = sh.run_of(uni(P.pre[b + 1]) - 1);
+        const bool at_start = pu <= sh.begin(x0 * subs);
+        s_cut[second] = CutPair{b, x0, x1 - x0 + 1, at_start ? slot_stride * x0 : (per_pair ? slot2 : 2 * x0 + 1)};
+      }
+    }
+  }
+  // Count the run in on its cut pairs once its stores are acknowledged; the last one merges.  The
+  // counter of a pair is its sequence's, or (of as many counters as runs) that of the run it starts
+  // in: at most one pair goes on past a run's end.
+  __builtin_amdgcn_s_waitcnt(PEARL_VMCNT(0));
+  __syncthreads();
+  const int task = threadIdx.x;                     // (slot kind, kv-head of the workgroup)
+  if (task < 2 * sh.heads) {
+    const int j = task >> 1;
+    const CutPair c = s_cut[task & 1];
+    int last = 0;
+    if (c.b >= 0) {
+      const int ctr = per_pair ? (g0 + j) * B + c.b : (g0 + j) * sh.n_runs + c.x0;
+      last = __hip_atomic_fetch_add(&a.split_cnt[ctr], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == c.n - 1;
+    }
+    s_last[task & 1][j] = last;
+  }
+  __syncthreads();
+  const int passes = (G + 3) / 4;
+#pragma unroll 1
+  for (int t = w; t < 2 * sh.heads * passes; t += NW) {
+    const int pair = t / passes;
+    if (s_last[pair & 1][pair >> 1])
+      merge_pair<D>(a, s_cut[pair & 1], g0 + (pair >> 1), slot_stride, d.max_dec, t - pair * passes);
   }
 }
 
-// Zeroes what the in-kernel decode plan needs zeroed: the workspace header (work counter, error
-// flag, the zero block) and the split counters.  A kernel, not a memset, so it can be captured.
+// Zeroes what the decode kernel needs zeroed: the workspace header (error flag, the zero block)
+// and the arrival counters.  A kernel, not a memset, so it can be captured.
 __global__ __launch_bounds__(256) void decode_prologue_kernel(int32_t* hdr, int32_t* split_cnt, int n_cnt) {
   for (int i = threadIdx.x; i < n_cnt; i += 256) split_cnt[i] = 0;
   if (threadIdx.x < kHdrWords) hdr[threadIdx.x] = 0;
@@ -1979,18 +2138,31 @@ hipError_t launch_attention(const AttnArgs& a, int head_dim, int kinds, int64_t 
   return hipGetLastError();
 }
 
-hipError_t launch_decode_prologue(const AttnArgs& a, int batch, hipStream_t stream) {
-  hipLaunchKernelGGL(decode_prologue_kernel, dim3(1), dim3(256), 0, stream, a.ws_hdr, a.split_cnt,
-                     batch * a.num_kv_heads);
+int decode_grid(int head_dim) {
+  const DevCache& c = dev_cache();
+  return c.num_cu * c.occ_dec[head_dim == 128 ? 1 : 0];
+}
+
+void set_decode_runs(DecPlanArgs& d, int num_kv_heads, int grid) {
+  // a run leaves at most two partials per head, the second ones also at most one per sequence
+  const int cap = std::max(1, std::max(d.max_dec / 2, d.max_dec - d.batch));
+  d.runs_one = std::min(grid / num_kv_heads, cap);
+  d.heads = std::min(num_kv_heads & -num_kv_heads, kWaves);
+  d.runs_heads = grid / (num_kv_heads / d.heads);
+  if (d.runs_heads > cap) {                         // not enough slots for a full grid of them
+    d.heads = 1;
+    d.runs_heads = 0;
+  }
+}
+
+hipError_t launch_decode_prologue(const AttnArgs& a, const DecPlanArgs& d, hipStream_t stream) {
+  // a counter per sequence and kv-head, or per run and kv-head if that is fewer
+  const int n = std::min(d.batch, std::max(d.runs_one, d.runs_heads)) * a.num_kv_heads;
+  hipLaunchKernelGGL(decode_prologue_kernel, dim3(1), dim3(256), 0, stream, a.ws_hdr, a.split_cnt, n);
   return hipGetLastError();
 }
 
-hipError_t launch_decode(const AttnArgs& a, const DecPlanArgs& d, int head_dim, int64_t max_items,
-                         hipStream_t stream) {
-  if (max_items <= 0) return hipSuccess;
-  const DevCache& c = dev_cache();
-  int64_t grid = (int64_t)c.num_cu * c.occ_dec[head_dim == 128 ? 1 : 0];
-  if (grid > max_items) grid = max_items;
+hipError_t launch_decode(const AttnArgs& a, const DecPlanArgs& d, int head_dim, int grid, hipStream_t stream) {
   if (head_dim == 64)
     hipLaunchKernelGGL(decode_kernel<64>, dim3((unsigned)grid), dim3(kThreads), 0, stream, a, d);
   else

@@ -43,6 +43,10 @@ constexpr int kNumXcd = 8;
 // Decode batches of up to this many sequences are planned inside the attention kernel (in LDS);
 // larger ones go through plan_kernel.
 constexpr int kDecPlanMaxSeqs = 1024;
+// Such a launch cuts each kv-head's list of pages into runs of at least kDecMinPages pages;
+// several kv-heads share a workgroup if its waves' shares hold kDecHeadPages pages or more.
+constexpr int kDecMinPages = 16;
+constexpr int kDecHeadPages = 64;
 
 enum Mode : int { kModePrefill = 0, kModeDecode = 1, kModeMixed = 2 };
 
@@ -116,7 +120,7 @@ struct AttnArgs {
   const int4* pre_jobs;      // (sequence, tile, first entry, splits) per split prefill tile
   float* part_pre_o;         // [slot][kRowsPerTile][D] unnormalised partial outputs
   float* part_pre_ml;        // [slot][kRowsPerTile][2] running max (log2 units) and sum
-  int32_t* split_cnt;        // [batch][num_kv_heads] splits finished per pair (decode planned in-kernel)
+  int32_t* split_cnt;        // arrival counters, at most batch * num_kv_heads (decode planned in-kernel)
   // fused append and decode (decode planned in-kernel only): the new token's K/V rows
   // [batch][num_kv_heads][D], or null; the pools again, writable
   const uint16_t* k_new;
@@ -137,8 +141,10 @@ struct DecPlanArgs {
   const int32_t* ctx_lens;
   int batch;
   int max_kv_len;
-  int pps_min;           // least pages per split (the host's bound, which sizes the workspace)
-  int max_dec;           // partial slots in the workspace
+  int max_dec;           // partial slots per kv-head in the workspace
+  int runs_one;          // runs of a kv-head's page list with one kv-head per workgroup (at most)
+  int heads;             // kv-heads of a workgroup that holds several (a power of two; 1: never)
+  int runs_heads;        // runs of the page list then
 };
 
 WsLayout workspace_layout(int batch, int total_q, int max_kv_len, int num_q_heads,
@@ -176,9 +182,12 @@ hipError_t launch_attention(const AttnArgs& a, int head_dim, int kinds, int64_t 
 hipError_t launch_merge(const AttnArgs& a, int head_dim, int batch, hipStream_t stream);
 
 // Decode planned in-kernel (batch <= kDecPlanMaxSeqs): the zeroing prologue, then the kernel.
-hipError_t launch_decode_prologue(const AttnArgs& a, int batch, hipStream_t stream);
-hipError_t launch_decode(const AttnArgs& a, const DecPlanArgs& d, int head_dim, int64_t max_items,
-                         hipStream_t stream);
+// grid: workgroups of a full grid (decode_grid), all resident.
+int decode_grid(int head_dim);
+// Sets d's run counts for such a grid (num_kv_heads <= grid), from d.batch and d.max_dec.
+void set_decode_runs(DecPlanArgs& d, int num_kv_heads, int grid);
+hipError_t launch_decode_prologue(const AttnArgs& a, const DecPlanArgs& d, hipStream_t stream);
+hipError_t launch_decode(const AttnArgs& a, const DecPlanArgs& d, int head_dim, int grid, hipStream_t stream);
 
 // Merge of split prefill tiles; jobs_cap bounds the device-side job count.
 hipError_t launch_merge_prefill(const AttnArgs& a, int head_dim, int64_t jobs_cap, hipStream_t stream);
