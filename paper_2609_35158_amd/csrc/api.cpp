@@ -117,8 +117,14 @@ Plan make_plan(const pearl_kv_shape* s, const pearl_seq_desc* q, int mode) {
   p.pages_per_split = pps;
   p.max_pre = pl.lay.max_pre;
   p.max_dec = pl.lay.max_dec;
-  p.pre_slots = mode == kModeDecode ? 0 : pl.lay.pre_slots;
-  p.pre_jobs_cap = mode == kModeDecode ? 0 : pl.lay.pre_jobs_cap;
+  // Prefill tiles may be split if the launch can hold few enough of them (the planner's rule, on the
+  // least tiles the token counts allow: in mixed launches up to one token per sequence is decode).
+  // With no split possible there is no prefill merge to launch.
+  const int64_t pre_tokens = mode == kModeMixed ? std::max(0, q->total_q - q->batch) : q->total_q;
+  const bool may_split = mode != kModeDecode && cdiv(pre_tokens, p.tokens_per_tile) * s->num_kv_heads <=
+                                                    (mode == kModeMixed ? kPlanComputeUnits : kPreSplitItems);
+  p.pre_slots = may_split ? pl.lay.pre_slots : 0;
+  p.pre_jobs_cap = may_split ? pl.lay.pre_jobs_cap : 0;
   p.mixed_grid = mode == kModeMixed ? attention_grid(s->head_dim, 3) : 0;
   return pl;
 }

@@ -119,25 +119,44 @@ template <int D, int NW, int kKinds> struct Lds {
 // ------------------------------------------------------------------------------------------------
 // Planner: one workgroup validates the device-resident lengths against the host bounds and
 // builds the work list (prefill q-tiles, then decode page-range splits), so no host sync is
-// needed.  Writes the header, per-sequence records and entries; zeroes the work counter.
+// needed.  Writes the header, per-sequence records and entries; zeroes the work counters.
 //
-// Prefill tiles are split along the keys when the launch holds at most one tile item per compute
-// unit and its longest tile would outlast the average work per unit.  Work is estimated in
-// key-units: a prefill tile key (256 q-rows on MFMA) costs about 3/2 of a decode key (one K/V row
-// read from HBM).  A split covers kKeysPerStage-aligned key ranges [s S, (s+1) S) of the tile,
-// the last one running to the tile's end; splits start at or before the first key that only
-// some rows of the tile see (key ctx + t0 + 1), so every row sees at least one key of every
-// split.  S is at least kMinSplitKeys and at least the tile keys per unit, which keeps the split
-// items of a launch under 2 * kPlanComputeUnits (the partial-slot capacity).
+// Prefill tiles are split along the keys when the launch has too few of them to fill the compute
+// units evenly.  All tiles of a sequence are cut at the same keys, multiples of its split_keys (the
+// record's kind field holds split_keys / kKeysPerStage), the last split running to the tile's end;
+// splits start at or before the first key that only some rows of the tile see (key ctx + t0 + 1),
+// so every row sees at least one key of every split.
+//   * Prefill launches of up to kPreSplitItems tile items: split_keys is the sequence's longest
+//     tile cut into equal parts of at most P stages, P being 0.6, 0.75, 1 or 1.5 of the launch's
+//     average stages per compute unit, whichever is the smallest whose splits fit the workspace's
+//     partial slots.  Longest first, two or three splits per unit end together; one split of the
+//     average length per unit leaves a second round of remainders: four turns of 91-392 tokens on
+//     14-23K contexts (176 items) took 367 stages on the busiest unit for an average of 228, and
+//     take 248 so (append, plan, attention and merge: 672 -> 459 us; 64-token chunks on 12-25K contexts
+//     at 4 kv-heads 236 -> 158).  With more items than kPreSplitItems whole tiles balance as well.
+//   * Mixed launches of up to one tile item per compute unit whose longest tile would outlast the
+//     average work per unit: split_keys is that average, at least kMinSplitKeys.  Work is estimated
+//     in key-units: a prefill tile key (256 q-rows on MFMA) costs about 3/2 of a decode key (one
+//     K/V row read from HBM).
+//
+// Prefill entries go longest first, in size classes, so the last entries a launch hands out are its
+// shortest ones; inside a class the tiles that read the same keys follow one another, so they run
+// at about the same time and share the caches.
 //
 // Decode splits hold pps pages each (the last one of a sequence the rest): pps is sized from the
 // launch's actual pages (about kDecItemsPerCU items per compute unit) but never below the host's
 // bound, so the workspace always holds the splits.  They are ordered longest first: every full
 // split, then the shorter last splits in kPartBuckets size classes, largest class first, so the
 // last items a launch hands out are its shortest ones.
+//
+// The kernel is latency from end to end (a first read of the lengths, then a few barriers, and the
+// instruction fetches of code that runs once), so loops are not unrolled.
 // ------------------------------------------------------------------------------------------------
 constexpr int kPlanThreads = 256;
+constexpr int kPlanWaves = kPlanThreads / 64;
 constexpr int kPartBuckets = 16;
+constexpr int kPreCandidates = 4;
+constexpr int kPlanKeep = 4;               // prefill entries a thread keeps between the planner's rounds
 
 // Size class of a short last split of `rest` pages (1 <= rest < pps); class 0 holds the longest.
 // inv_pps = kPartBuckets / pps; the class only orders work, so rounding at a class edge is harmless.
@@ -145,84 +164,123 @@ __device__ __forceinline__ int part_bucket(int rest, float inv_pps) {
   return kPartBuckets - 1 - min(kPartBuckets - 1, (int)((float)(rest - 1) * inv_pps));
 }
 
-// Size class of an unsplit prefill tile whose first row sees `keys` keys (at most max_full;
-// inv_keys = kPartBuckets / (max_full + 1)): the longest tiles are class 0.
-__device__ __forceinline__ int tile_class(int keys, float inv_keys) {
-  return kPartBuckets - 1 - min(kPartBuckets - 1, (int)((float)keys * inv_keys));
-}
-
 __device__ __forceinline__ int tile_splits(int ctx, int t0, int split_keys) {
   return split_keys > 0 ? (ctx + t0 + split_keys) / split_keys : 1;   // ceil((ctx + t0 + 1) / S)
 }
 
+__device__ __forceinline__ int key_stages(int keys) { return (keys + kKeysPerStage - 1) / kKeysPerStage; }
+
+// split_keys of a sequence whose longest tile holds `stages` stages, for splits of at most P stages
+// (0: whole tiles).
+__device__ __forceinline__ int seq_split_keys(int stages, int P) {
+  if (P <= 0 || stages <= P) return 0;
+  const int ns = (stages + P - 1) / P;
+  return (stages + ns - 1) / ns * kKeysPerStage;
+}
+
+struct PlanSeq { int ctx, q_len, split_keys; };
+
+// kMode: kModePrefill, kModeDecode or kModeMixed.
+template <int kMode>
 __global__ __launch_bounds__(kPlanThreads) void plan_kernel(
     PlanParams p, const int32_t* __restrict__ ctx_lens, const int32_t* __restrict__ cu,
     int32_t* __restrict__ hdr, SeqInfo* __restrict__ seqinfo, int32_t* __restrict__ split_base,
     int2* __restrict__ entries, int4* __restrict__ pre_jobs) {
-  __shared__ int s_err, s_tiles, s_max_full, s_split_keys, s_pre_first;
-  __shared__ unsigned long long s_pre_keys, s_dec_keys;
-  __shared__ int s_wave[4][kPlanThreads / 64];
-  __shared__ int s_carry[4];
-  __shared__ int s_n_full;                     // full decode splits of the launch
-  __shared__ int s_pps;                        // pages per decode split
-  __shared__ unsigned long long s_dec_pages;
-  __shared__ int s_part_cnt[kPartBuckets];     // short last splits per size class, then fill counts
-  __shared__ int s_part_off[kPartBuckets];     // first position of each size class after the full splits
-  __shared__ int s_tile_cnt[kPartBuckets];     // unsplit prefill tiles per size class, then fill counts
-  __shared__ int s_tile_off[kPartBuckets];     // first prefill entry of each size class
-  const int tid = threadIdx.x;
-  const int T = p.tokens_per_tile;
-  if (tid == 0) {
-    s_err = 0; s_tiles = 0; s_max_full = 0; s_pre_keys = 0; s_dec_keys = 0; s_n_full = 0; s_dec_pages = 0;
-    s_carry[0] = s_carry[1] = s_carry[2] = s_carry[3] = 0;
-  }
+  __shared__ unsigned long long s_sum[2][kPlanWaves];      // prefill key-units, decode keys
+  __shared__ int s_pages[kPlanWaves];                      // decode pages
+  __shared__ int s_tiles[kPlanWaves], s_longest[kPlanWaves], s_bad[kPlanWaves];
+  __shared__ int s_fits[kPreCandidates];                   // of each candidate P
+  __shared__ int s_wave[4][kPlanWaves];
+  __shared__ int s_part_cnt[kPartBuckets], s_part_off[kPartBuckets];   // short last decode splits
+  __shared__ int s_tile_cnt[kPartBuckets], s_tile_off[kPartBuckets];   // prefill entries
+  __shared__ int s_jobs;
+  __shared__ PlanSeq s_seq[kPlanThreads];                  // a chunk's prefill sequences
+  __shared__ int s_pre[kPlanThreads + 1];                  // prefix sums of their candidate entries
+  __shared__ int s_slot[kPlanThreads];                     // their first partial slots
+  __shared__ SeqInfo s_first[kPlanThreads];                // the first chunk's sequences
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int T = p.tokens_per_tile, H = p.num_kv_heads;
+  // counts scanned per sequence: decode splits, full decode splits, candidate prefill entries, slots
+  constexpr int C0 = kMode == kModePrefill ? 2 : 0, C1 = kMode == kModeDecode ? 2 : 4;
+  const int log_t = __builtin_ctz(T);               // T is a power of two
+  auto tiles_of = [&](int q_len) { return (q_len + T - 1) >> log_t; };
+  const int chunks = (p.batch + kPlanThreads - 1) / kPlanThreads;
   if (tid < kPartBuckets) { s_part_cnt[tid] = 0; s_tile_cnt[tid] = 0; }
+  if (tid == 0) s_jobs = 0;
   if (tid < kHdrWords - kHdrZero) hdr[kHdrZero + tid] = 0;   // zero block read by decode items
   if (tid < kNumXcd) hdr[kHdrQueues + tid] = 0;
-  __syncthreads();
+  // sequence b's lengths
+  auto seq_of = [&](int b) {
+    SeqInfo s{b, 1, ctx_lens[b], kSeqNone};
+    if (cu) {
+      s.q_start = cu[b];
+      s.q_len = cu[b + 1] - s.q_start;
+    }
+    if (s.q_len > 0)
+      s.kind = kMode == kModeDecode || (kMode == kModeMixed && s.q_len == 1) ? kSeqDecode : kSeqPrefill;
+    return s;
+  };
   // pass 1: validate every sequence and total the work
-  // sequence tid's lengths (first chunk), kept for the later passes
-  int my_pages = 0, my_q_start = 0, my_q_len = 0, my_ctx = 0;
+  SeqInfo mine{0, 0, 0, kSeqNone};                  // of the first chunk
   {
-    int tiles = 0, max_full = 0;
-    unsigned long long pre_keys = 0, dec_keys = 0, dec_pages = 0;
+    int tiles = 0, longest = 0, dpages = 0;         // pages: batch * bt_stride fits 32 bits
+    unsigned long long sum[2] = {0, 0};
+    bool bad = false;
+#pragma unroll 1
     for (int b = tid; b < p.batch; b += kPlanThreads) {
-      const int q_start = cu ? cu[b] : b;
-      const int q_len = cu ? cu[b + 1] - q_start : 1;
-      const int ctx = ctx_lens[b];
-      if (b == tid) {
-        my_q_start = q_start;
-        my_q_len = q_len;
-        my_ctx = ctx;
-      }
-      const long long kv = (long long)ctx + q_len;
-      bool bad = q_len < 0 || ctx < 0 || q_start < 0 || q_len > p.max_q_len ||
-                 (long long)q_start + q_len > p.total_q || kv > p.max_kv_len ||
-                 (kv + kPage - 1) / kPage > p.bt_stride;
-      if (p.mode == kModeDecode && q_len != 1) bad = true;
-      if (bad) { atomicOr(&s_err, 1); continue; }
-      if (q_len <= 0) continue;
-      if (p.mode == kModeDecode || (p.mode == kModeMixed && q_len == 1)) {
-        dec_keys += (unsigned long long)kv;
-        const int pages = (int)((kv + kPage - 1) / kPage);
-        dec_pages += (unsigned long long)pages;
-        if (b == tid) my_pages = pages;
-      } else {
-        const int nt = (q_len + T - 1) / T;
+      const SeqInfo s = seq_of(b);
+      if (b == tid) s_first[tid] = mine = s;
+      const long long kv = (long long)s.ctx_len + s.q_len;
+      if (s.q_len < 0 || s.ctx_len < 0 || s.q_start < 0 || s.q_len > p.max_q_len ||
+          (long long)s.q_start + s.q_len > p.total_q || kv > p.max_kv_len || (kv + kPage - 1) / kPage > p.bt_stride ||
+          (kMode == kModeDecode && s.q_len != 1)) {
+        bad = true;
+      } else if (kMode != kModePrefill && s.kind == kSeqDecode) {
+        sum[1] += (unsigned long long)kv;
+        dpages += (int)((kv + kPage - 1) / kPage);
+      } else if (kMode != kModeDecode && s.kind == kSeqPrefill) {
+        const int nt = tiles_of(s.q_len);
         tiles += nt;
         // keys seen by every row of tile t: ctx + t T + 1
-        pre_keys += (unsigned long long)nt * (ctx + 1) + (unsigned long long)T * nt * (nt - 1) / 2;
-        max_full = max(max_full, ctx + (nt - 1) * T + 1);
+        sum[0] += (unsigned long long)nt * (s.ctx_len + 1) + (unsigned long long)T * nt * (nt - 1) / 2;
+        longest = max(longest, (int)kv);
       }
     }
-    if (tiles) atomicAdd(&s_tiles, tiles);
-    if (dec_pages) atomicAdd(&s_dec_pages, dec_pages);
-    if (max_full) atomicMax(&s_max_full, max_full);
-    if (pre_keys) atomicAdd(&s_pre_keys, pre_keys);
-    if (dec_keys) atomicAdd(&s_dec_keys, dec_keys);
+#pragma unroll 1
+    for (int off = 32; off >= 1; off >>= 1) {
+      if (kMode != kModeDecode) {
+        tiles += __shfl_xor(tiles, off);
+        longest = max(longest, __shfl_xor(longest, off));
+        sum[0] += __shfl_xor(sum[0], off);
+      }
+      if (kMode != kModePrefill) {
+        sum[1] += __shfl_xor(sum[1], off);
+        dpages += __shfl_xor(dpages, off);
+      }
+    }
+    const bool wave_bad = __any(bad);
+    if (lane == 0) {
+      s_tiles[wv] = tiles;
+      s_longest[wv] = longest;
+      s_bad[wv] = wave_bad;
+      s_sum[0][wv] = sum[0];
+      s_sum[1][wv] = sum[1];
+      s_pages[wv] = dpages;
+    }
   }
   __syncthreads();
-  if (s_err) {
+  int tiles = 0, longest = 0, bad = 0;
+  unsigned long long pre_keys = 0, dec_keys = 0, dec_pages = 0;
+#pragma unroll
+  for (int w = 0; w < kPlanWaves; ++w) {
+    tiles += s_tiles[w];
+    longest = max(longest, s_longest[w]);
+    bad |= s_bad[w];
+    pre_keys += s_sum[0][w];
+    dec_keys += s_sum[1][w];
+    dec_pages += s_pages[w];
+  }
+  if (bad) {
     if (tid == 0) {
       hdr[kHdrCounter] = 0; hdr[kHdrNumPre] = 0; hdr[kHdrNumDec] = 0;
       hdr[kHdrError] = 1; hdr[kHdrNumItems] = 0; hdr[kHdrPreSplitKeys] = 0; hdr[kHdrNumPreJobs] = 0;
@@ -230,199 +288,257 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(
     }
     return;
   }
-  if (tid == 0) {
-    long long S = 0;
-    const long long H = p.num_kv_heads;
-    if (p.pre_slots > 0 && s_tiles > 0 && (long long)s_tiles * H <= kPlanComputeUnits) {
-      const long long pre_units = (long long)s_pre_keys * H;
-      const long long work = pre_units + pre_units / 2 + (long long)s_dec_keys * H;
-      const long long per_cu = (work + kPlanComputeUnits - 1) / kPlanComputeUnits;
-      S = max((long long)kMinSplitKeys, (pre_units + kPlanComputeUnits - 1) / kPlanComputeUnits);
-      S = max(S, (2 * per_cu + 2) / 3);
-      S = (S + kKeysPerStage - 1) / kKeysPerStage * kKeysPerStage;
-      if (S >= s_max_full) S = 0;            // no tile would split
+  // Prefill splits: the first of the candidates whose entries and partial slots fit.  P: the most
+  // stages of a split (prefill launches); mixed_keys: split_keys of every sequence (mixed ones).
+  const long long pre_units = (long long)pre_keys * H;
+  int P = 0, mixed_keys = 0;
+  constexpr bool is_mixed = kMode == kModeMixed;
+  if (kMode != kModeDecode && p.pre_slots > 0 && tiles > 0 && (long long)tiles * H <= (is_mixed ? kPlanComputeUnits : kPreSplitItems)) {
+    const long long work = pre_units + pre_units / 2 + (long long)dec_keys * H;
+    const long long per_cu = (work + kPlanComputeUnits - 1) / kPlanComputeUnits;
+    const long long share_keys = (pre_units + kPlanComputeUnits - 1) / kPlanComputeUnits;
+    const int share = (int)((share_keys + kKeysPerStage - 1) / kKeysPerStage);
+    const int S0 = max(kMinSplitKeys / kKeysPerStage,
+                       max(share, (int)(((2 * per_cu + 2) / 3 + kKeysPerStage - 1) / kKeysPerStage)));
+    constexpr int kLeast = kMinSplitKeys / kKeysPerStage;
+    auto cand = [&](int c) {                        // stages
+      if (is_mixed) return S0 << c;
+      return c == 0 ? max(kLeast / 2, (3 * share + 4) / 5)
+                    : c == 1 ? max(kLeast / 2, (3 * share + 3) / 4) : max(kLeast, c == 2 ? share : share + share / 2);
+    };
+    static_assert(kPlanWaves == kPreCandidates, "a wave per candidate");
+    const int my_cand = cand(wv);
+    int n_entries = 0, n_slots = 0;
+#pragma unroll 1
+    for (int b = lane; b < p.batch; b += 64) {
+      const SeqInfo s = b < kPlanThreads ? s_first[b] : seq_of(b);
+      if (s.kind != kSeqPrefill) continue;
+      const int nt = tiles_of(s.q_len);
+      const int S = is_mixed ? my_cand * kKeysPerStage : seq_split_keys(key_stages(s.ctx_len + s.q_len), my_cand);
+      const int n = nt * tile_splits(s.ctx_len, (nt - 1) * T, S);
+      n_entries += n;
+      if (S > 0) n_slots += n;
     }
-    s_split_keys = (int)S;
+#pragma unroll 1
+    for (int off = 32; off >= 1; off >>= 1) {
+      n_entries += __shfl_xor(n_entries, off);
+      n_slots += __shfl_xor(n_slots, off);
+    }
+    if (lane == 0) s_fits[wv] = n_entries <= p.max_pre && (long long)n_slots * H <= p.pre_slots && n_slots <= p.pre_jobs_cap;
+    __syncthreads();
+#pragma unroll
+    for (int c = kPreCandidates - 1; c >= 0; --c)
+      if (s_fits[c]) P = cand(c);
+    if (P >= key_stages(longest)) P = 0;            // no tile would split
+    if (is_mixed) {
+      mixed_keys = P * kKeysPerStage;
+      P = 0;
+    }
+  }
+  auto split_of = [&](const SeqInfo& s) {
+    return mixed_keys > 0 ? mixed_keys : seq_split_keys(key_stages(s.ctx_len + s.q_len), P);
+  };
+  // Decode split size: about kDecItemsPerCU items per compute unit over the launch's actual
+  // pages, a multiple of 16 pages, at least the host's bound and at most kMaxPagesPerSplit.
+  // Splits of at least kDecLongSplitPages pages (16 pages per wave) while that still leaves
+  // 2 items per compute unit: a wave's first page of an item waits unhidden, so short splits
+  // pay it often.
+  int pps = p.pages_per_split;
+  if (kMode != kModePrefill && dec_pages > 0) {
+    const unsigned long long units = dec_pages * H;
+    const unsigned long long per = (unsigned long long)kPlanComputeUnits * kDecItemsPerCU;
+    const unsigned long long want = (units + per - 1) / per, two = (units + 2 * kPlanComputeUnits - 1) / (2 * kPlanComputeUnits);
+    const unsigned long long top = max(p.pages_per_split, kMaxPagesPerSplit);
+    pps = max(pps, (int)min(top, (want + 15) / 16 * 16));
+    pps = max(pps, (int)min((unsigned long long)kDecLongSplitPages, (two + 15) / 16 * 16));
+  }
+  const float inv_pps = (float)kPartBuckets / (float)pps;
+  // size classes of prefill entries, by their stages; the longest possible entry is in class 0
+  const int max_stages = mixed_keys > 0 ? mixed_keys / kKeysPerStage : (P > 0 ? P : key_stages(longest));
+  const float inv_stages = (float)kPartBuckets / (float)(max_stages + 1);
+  // The sequences, a chunk at a time: round 0 counts the classes, round 1 writes the records and the
+  // entries.  Usually there is one chunk and each thread has at most kPlanKeep prefill entries: it
+  // keeps what round 0 found (class and rank in it), and round 1 only writes.
+  int carry[4] = {0, 0, 0, 0};
+  int keep_pos[kPlanKeep], keep_code[kPlanKeep], keep_seq[kPlanKeep];
+  bool keeps = false;
+  int cnt[4], excl[4] = {0, 0, 0, 0}, total[4] = {0, 0, 0, 0}, rest = 0, split_keys = 0, part_class = 0, part_rank = 0;
+  SeqInfo s = mine;
+  auto keeps_now = [&](int chunk, int entries_) { return chunk == 0 && chunks == 1 && entries_ <= kPlanKeep * kPlanThreads; };
+#pragma unroll 1
+  for (int round = 0; round < 2; ++round) {
+    if (!keeps) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) carry[c] = 0;
+    }
+#pragma unroll 1
+    for (int chunk = 0; chunk < chunks; ++chunk) {
+      const int b = chunk * kPlanThreads + tid;
+      if (!keeps) {
+        s = SeqInfo{0, 0, 0, kSeqNone};
+        if (b < p.batch) s = chunk == 0 ? mine : seq_of(b);
+        // decode splits, full decode splits, candidate prefill entries, partial slots
+#pragma unroll
+        for (int c = 0; c < 4; ++c) cnt[c] = 0;
+        rest = split_keys = 0;
+        if (kMode != kModePrefill && s.kind == kSeqDecode) {
+          const int pages = (s.ctx_len + s.q_len + kPage - 1) / kPage;
+          cnt[0] = (pages + pps - 1) / pps;
+          cnt[1] = pages / pps;
+          rest = pages - cnt[1] * pps;
+        } else if (kMode != kModeDecode && s.kind == kSeqPrefill) {
+          const int nt = tiles_of(s.q_len);
+          split_keys = split_of(s);
+          cnt[2] = nt * tile_splits(s.ctx_len, (nt - 1) * T, split_keys);
+          cnt[3] = split_keys > 0 ? cnt[2] : 0;
+        }
+        // exclusive scan: wave-level inclusive scans by shuffles, then the totals of earlier waves
+        int incl[4] = {cnt[0], cnt[1], cnt[2], cnt[3]};
+#pragma unroll 1
+        for (int off = 1; off < 64; off <<= 1) {
+#pragma unroll
+          for (int c = C0; c < C1; ++c) {
+            const int u = __shfl_up(incl[c], off);
+            if (lane >= off) incl[c] += u;
+          }
+        }
+        if (lane == 63) {
+#pragma unroll
+          for (int c = C0; c < C1; ++c) s_wave[c][wv] = incl[c];
+        }
+        if (rest) {
+          part_class = part_bucket(rest, inv_pps);
+          part_rank = atomicAdd(&s_part_cnt[part_class], 1);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int c = C0; c < C1; ++c) {
+          int before = 0;
+          total[c] = 0;
+#pragma unroll
+          for (int w = 0; w < kPlanWaves; ++w) {
+            if (w < wv) before += s_wave[c][w];
+            total[c] += s_wave[c][w];
+          }
+          excl[c] = carry[c] + before + incl[c] - cnt[c];
+        }
+        s_seq[tid] = PlanSeq{s.ctx_len, s.q_len, split_keys};
+        s_slot[tid] = excl[3];
+        s_pre[tid + 1] = excl[2] - carry[2] + cnt[2];
+        if (tid == 0) s_pre[0] = 0;
+        __syncthreads();
+      }
+      if (round && b < p.batch) {
+        seqinfo[b] = SeqInfo{s.q_start, s.q_len, s.ctx_len,
+                             s.kind == kSeqPrefill ? kSeqPrefill | (split_keys / kKeysPerStage << 4) : s.kind | (cnt[0] << 4)};
+        split_base[b] = s.kind == kSeqPrefill ? excl[3] : excl[0];
+        // full splits in sequence order, the short last split at its size class's next position
+        const int part_pos = rest ? s_part_off[part_class] + part_rank : 0;
+#pragma unroll 1
+        for (int sp = 0; sp < cnt[0]; ++sp) {
+          const int pos = sp < cnt[1] ? excl[1] + sp : part_pos;
+          if (pos < p.max_dec) entries[p.max_pre + pos] = make_int2(b, sp);
+        }
+      }
+      // Prefill entries, a thread each: (split, tile) of a sequence, the tile running fastest, last
+      // tile first.  Returns the entry's class and rank, or -1 if there is none (shorter tiles of a
+      // sequence have fewer splits).
+      auto find = [&](int i, int& lo, int& code, int& rank) {
+        lo = 0;
+        int hi = min(kPlanThreads, p.batch - chunk * kPlanThreads) - 1;
+        while (lo < hi) {                           // the last sequence whose entries start at or before i
+          const int mid = (lo + hi + 1) >> 1;
+          if (s_pre[mid] <= i) lo = mid; else hi = mid - 1;
+        }
+        const PlanSeq q = s_seq[lo];
+        const int nt = tiles_of(q.q_len), j = i - s_pre[lo];
+        const int sp = j / nt, t = nt - 1 - (j - sp * nt);
+        const int ns = tile_splits(q.ctx, t * T, q.split_keys);
+        if (sp >= ns) return -1;
+        const int step = q.split_keys / kKeysPerStage;
+        const int stages = sp + 1 < ns ? step : key_stages(q.ctx + min(q.q_len, (t + 1) * T)) - sp * step;
+        const int k = kPartBuckets - 1 - min(kPartBuckets - 1, (int)((float)stages * inv_stages));
+        code = t | (sp << 16);
+        rank = atomicAdd(&s_tile_cnt[k], 1);
+        if (round == (keeps_now(chunk, total[2]) ? 0 : 1) && sp == 0 && ns > 1) {
+          const int job = atomicAdd(&s_jobs, 1);
+          if (job < p.pre_jobs_cap) pre_jobs[job] = make_int4(chunk * kPlanThreads + lo, t, s_slot[lo] + t, ns);
+        }
+        return k;
+      };
+      if (!keeps && keeps_now(chunk, total[2])) {
+#pragma unroll
+        for (int u = 0; u < kPlanKeep; ++u) {
+          keep_pos[u] = -1;
+          const int i = tid + u * kPlanThreads;
+          if (i < total[2]) {
+            int rank = 0;
+            const int k = find(i, keep_seq[u], keep_code[u], rank);
+            if (k >= 0) keep_pos[u] = k << 24 | rank;
+          }
+        }
+      } else if (keeps) {
+#pragma unroll
+        for (int u = 0; u < kPlanKeep; ++u) {
+          if (keep_pos[u] < 0) continue;
+          const int pos = s_tile_off[keep_pos[u] >> 24] + (keep_pos[u] & 0xffffff);
+          if (pos < p.max_pre) entries[pos] = make_int2(keep_seq[u], keep_code[u]);
+        }
+      } else {
+#pragma unroll 1
+        for (int i = tid; i < total[2]; i += kPlanThreads) {
+          int lo, code = 0, rank = 0;
+          const int k = find(i, lo, code, rank);
+          if (!round || k < 0) continue;
+          const int pos = s_tile_off[k] + rank;
+          if (pos < p.max_pre) entries[pos] = make_int2(chunk * kPlanThreads + lo, code);
+        }
+      }
+      if (!keeps) {
+        __syncthreads();
+#pragma unroll
+        for (int c = C0; c < C1; ++c) carry[c] += total[c];
+      }
+    }
+    if (round == 0) {
+      // offsets of the classes, largest first (decode: after the full splits)
+      if (tid < kPartBuckets) {
+        int off = carry[1], toff = 0;
+#pragma unroll
+        for (int k = 0; k < kPartBuckets; ++k) {    // all reads in flight together
+          const int c = s_part_cnt[k], t = s_tile_cnt[k];
+          if (k < tid) { off += c; toff += t; }
+        }
+        s_part_off[tid] = off;
+        s_tile_off[tid] = toff;
+      }
+      keeps = keeps_now(0, total[2]);
+      __syncthreads();
+      if (!keeps) {
+        if (tid < kPartBuckets) { s_part_cnt[tid] = 0; s_tile_cnt[tid] = 0; }   // now the fill counts
+        __syncthreads();
+      }
+    }
+  }
+  if (tid == 0) {
+    const int n_pre = s_tile_off[kPartBuckets - 1] + s_tile_cnt[kPartBuckets - 1];
+    const int n_dec = carry[0], n_jobs = s_jobs;
+    const bool over = n_pre > p.max_pre || n_dec > p.max_dec || n_jobs > p.pre_jobs_cap ||
+                      (long long)carry[3] * H > p.pre_slots;
     // Mixed launches: how many workgroups take prefill items first (the others take decode items
     // first): 1.2 x prefill's share of the estimated work, in prefill and decode key-units
     // weighted 3 : 2 as above.  A prefill tile left for the end of a launch holds one workgroup
     // far longer than a decode split, so prefill gets more than its share.
-    int pre_first = 0;
-    if (p.mixed_grid > 0) {
-      const long long pu = 3LL * (long long)s_pre_keys * H;
-      const long long du = 2LL * (long long)s_dec_keys * H;
-      pre_first = pu + du > 0 ? (int)min((long long)p.mixed_grid, (6LL * p.mixed_grid * pu) / (5 * (pu + du)))
-                              : p.mixed_grid;
+    if (kMode == kModeMixed) {
+      const double pu = 3.0 * (double)pre_units, du = 2.0 * (double)((long long)dec_keys * H);
+      hdr[kHdrPreFirstWG] = pu + du > 0 ? (int)fmin((double)p.mixed_grid, 1.2 * p.mixed_grid * pu / (pu + du)) : p.mixed_grid;
     }
-    s_pre_first = pre_first;
-    // Decode split size: about kDecItemsPerCU items per compute unit over the launch's actual
-    // pages, a multiple of 16 pages, at least the host's bound and at most kMaxPagesPerSplit.
-    // Splits of at least kDecLongSplitPages pages (16 pages per wave) while that still leaves
-    // 2 items per compute unit: a wave's first page of an item waits unhidden, so short splits
-    // pay it often.
-    long long pps = p.pages_per_split;
-    if (s_dec_pages > 0) {
-      const long long units = (long long)s_dec_pages * H;
-      const long long per = (long long)kPlanComputeUnits * kDecItemsPerCU;
-      const long long want = (units + per - 1) / per;
-      const long long two = (units + 2LL * kPlanComputeUnits - 1) / (2LL * kPlanComputeUnits);
-      pps = max(pps, (want + 15) / 16 * 16);
-      pps = max(pps, min((long long)kDecLongSplitPages, (two + 15) / 16 * 16));
-      pps = min(pps, (long long)max(p.pages_per_split, kMaxPagesPerSplit));
-    }
-    s_pps = (int)pps;
-  }
-  __syncthreads();
-  const int pps = s_pps;
-  const float inv_pps = (float)kPartBuckets / (float)pps;
-  const int S = s_split_keys;
-  const float inv_keys = (float)kPartBuckets / (float)(s_max_full + 1);
-  // pass 1b: full decode splits and the size classes of the short last splits; without key
-  // splits, the size classes of the prefill tiles too
-  {
-    int n_full = 0;
-    for (int b = tid; b < p.batch; b += kPlanThreads) {
-      int pages = my_pages, q_len = my_q_len, ctx = my_ctx;
-      bool dec = pages > 0;
-      if (b != tid) {
-        const int q_start = cu ? cu[b] : b;
-        q_len = cu ? cu[b + 1] - q_start : 1;
-        ctx = ctx_lens[b];
-        dec = p.mode == kModeDecode || (p.mode == kModeMixed && q_len == 1);
-        pages = dec ? (ctx + q_len + kPage - 1) / kPage : 0;
-      }
-      if (pages > 0) {
-        const int rest = pages % pps;
-        n_full += pages / pps;
-        if (rest) atomicAdd(&s_part_cnt[part_bucket(rest, inv_pps)], 1);
-      } else if (!dec && q_len > 0 && S == 0) {
-        const int nt = (q_len + T - 1) / T;
-        for (int t = 0; t < nt; ++t) atomicAdd(&s_tile_cnt[tile_class(ctx + t * T + 1, inv_keys)], 1);
-      }
-    }
-    if (n_full) atomicAdd(&s_n_full, n_full);
-  }
-  __syncthreads();
-  if (tid < kPartBuckets) {                   // size classes, largest first (decode: after the full splits)
-    int off = s_n_full, toff = 0;
-    for (int k = 0; k < tid; ++k) { off += s_part_cnt[k]; toff += s_tile_cnt[k]; }
-    s_part_off[tid] = off;
-    s_tile_off[tid] = toff;
-  }
-  __syncthreads();
-  if (tid < kPartBuckets) { s_part_cnt[tid] = 0; s_tile_cnt[tid] = 0; }   // now the fill counts
-  __syncthreads();
-  // pass 2: per-sequence counts (prefill entries, decode splits, split tiles, full decode splits),
-  // block-wide exclusive scans, then the entries: prefill tiles longest first (unsplit tiles by
-  // size class across the launch; key-split tiles per sequence, last tile first, splits in
-  // order); decode splits longest first (full splits, then size classes)
-  for (int base = 0; base < p.batch; base += kPlanThreads) {
-    const int b = base + tid;
-    int cnt[4] = {0, 0, 0, 0};              // prefill entries, decode splits, split tiles, full decode splits
-    int kind = kSeqNone, q_start = 0, q_len = 0, ctx = 0, nt = 0, rest = 0;
-    if (b < p.batch) {
-      q_start = base == 0 ? my_q_start : (cu ? cu[b] : b);
-      q_len = base == 0 ? my_q_len : (cu ? cu[b + 1] - q_start : 1);
-      ctx = base == 0 ? my_ctx : ctx_lens[b];
-      if (q_len > 0) {
-        const bool dec = p.mode == kModeDecode || (p.mode == kModeMixed && q_len == 1);
-        if (dec) {
-          const int pages = (ctx + q_len + kPage - 1) / kPage;
-          kind = kSeqDecode;
-          cnt[1] = (pages + pps - 1) / pps;
-          cnt[3] = pages / pps;
-          rest = pages - cnt[3] * pps;
-        } else {
-          kind = kSeqPrefill;
-          nt = (q_len + T - 1) / T;
-          for (int t = 0; t < nt; ++t) {
-            const int ns = tile_splits(ctx, t * T, S);
-            cnt[0] += ns;
-            cnt[2] += ns > 1;
-          }
-        }
-      }
-    }
-    // exclusive scan: wave-level inclusive scans by shuffles, then the totals of earlier waves
-    const int lane = tid & 63, wv = tid >> 6;
-    int incl[4] = {cnt[0], cnt[1], cnt[2], cnt[3]};
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const int v = __shfl_up(incl[c], off);
-        if (lane >= off) incl[c] += v;
-      }
-    }
-    if (lane == 63) {
-#pragma unroll
-      for (int c = 0; c < 4; ++c) s_wave[c][wv] = incl[c];
-    }
-    __syncthreads();
-    int excl[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      int before = s_carry[c];
-      for (int k = 0; k < wv; ++k) before += s_wave[c][k];
-      excl[c] = before + incl[c] - cnt[c];
-    }
-    if (b < p.batch) {
-      seqinfo[b] = SeqInfo{q_start, q_len, ctx, kind | (cnt[1] << 4)};
-      split_base[b] = excl[1];
-      if (S == 0) {
-        // unsplit tiles go longest first across the whole launch (by size class), so the last
-        // tiles the persistent grid hands out are short ones from any sequence.  A sequence's
-        // tiles of one class (a run of consecutive tiles) are claimed together and stay
-        // adjacent, so the tiles that read the same K/V still run at about the same time.
-        for (int t = nt - 1; t >= 0;) {
-          const int k = tile_class(ctx + t * T + 1, inv_keys);
-          int t_end = t;
-          while (t_end > 0 && tile_class(ctx + (t_end - 1) * T + 1, inv_keys) == k) --t_end;
-          int pos = s_tile_off[k] + atomicAdd(&s_tile_cnt[k], t - t_end + 1);
-          for (; t >= t_end; --t, ++pos)
-            if (pos < p.max_pre) entries[pos] = make_int2(b, t);
-        }
-      } else {
-        // key-split tiles: each tile's splits stay contiguous (their partial slots follow the
-        // entry index), last tile of the sequence first
-        int e = excl[0], j = excl[2];
-        for (int t = nt - 1; t >= 0; --t) {
-          const int ns = tile_splits(ctx, t * T, S);
-          if (ns > 1 && j < p.pre_jobs_cap) pre_jobs[j++] = make_int4(b, t, e, ns);
-          for (int sp = 0; sp < ns; ++sp, ++e)
-            if (e < p.max_pre) entries[e] = make_int2(b, t | (sp << 16));
-        }
-      }
-      // full splits in sequence order; the short last split at its size class's next position
-      // (claimed before the loop, so the wave issues the atomic once)
-      int part_pos = 0;
-      if (rest) {
-        const int k = part_bucket(rest, inv_pps);
-        part_pos = s_part_off[k] + atomicAdd(&s_part_cnt[k], 1);
-      }
-      for (int sp = 0; sp < cnt[1]; ++sp) {
-        const int pos = sp < cnt[3] ? excl[3] + sp : part_pos;
-        if (pos < p.max_dec) entries[p.max_pre + pos] = make_int2(b, sp);
-      }
-    }
-    __syncthreads();
-    if (tid == kPlanThreads - 1) {
-#pragma unroll
-      for (int c = 0; c < 4; ++c) s_carry[c] = excl[c] + cnt[c];
-    }
-    __syncthreads();
-  }
-  if (tid == 0) {
-    const int n_pre = s_carry[0], n_dec = s_carry[1], n_jobs = s_carry[2];
-    const bool over = n_pre > p.max_pre || n_dec > p.max_dec || n_jobs > p.pre_jobs_cap ||
-                      (n_jobs > 0 && (long long)n_pre * p.num_kv_heads > p.pre_slots);
     hdr[kHdrCounter] = 0;
-    hdr[kHdrPreFirstWG] = s_pre_first;
     hdr[kHdrNumPre] = over ? 0 : n_pre;
     hdr[kHdrNumDec] = over ? 0 : n_dec;
     hdr[kHdrError] = over ? 2 : 0;
-    hdr[kHdrNumItems] = over ? 0 : (n_pre + n_dec) * p.num_kv_heads;
-    hdr[kHdrPreSplitKeys] = S;
+    hdr[kHdrNumItems] = over ? 0 : (n_pre + n_dec) * H;
+    hdr[kHdrPreSplitKeys] = mixed_keys > 0 ? mixed_keys : P * kKeysPerStage;
     hdr[kHdrNumPreJobs] = over ? 0 : n_jobs;
     hdr[kHdrPagesPerSplit] = pps;
   }
@@ -500,8 +616,9 @@ template <int D, int KEYS = kKeysPerStage> struct DmaTile {
 //   O^T (dims x rows) += V^T . P^T  (A = V^T via LDS transpose reads, B = P^T from S^T registers)
 // Each lane owns one q-row (l%32) for both products, so the softmax row statistics are
 // lane-local apart from one exchange with lane l^32, which holds the row's other keys.
-// A split item (entry e, code = tile | split << 16) covers only its key range and writes the
-// unnormalised (o~, m, l) of its rows to partial slot e * H_kv + g for the prefill merge.
+// A split item (code = tile | split << 16) covers only its key range and writes the unnormalised
+// (o~, m, l) of its rows to partial slot (base + split * tiles + tile) * H_kv + g, base being its
+// sequence's split_base, for the prefill merge.
 //
 // Schedule (prefill-only and mixed kernels): the matrix and vector work of the two waves on each
 // SIMD overlap.  The 8 waves form two groups, waves 0-3 and waves 4-7 (the waves w and w + 4 share
@@ -526,8 +643,7 @@ template <int D, int KEYS = kKeysPerStage> struct DmaTile {
 // (the copies issued since stay in flight).
 // ------------------------------------------------------------------------------------------------
 template <int D>
-__device__ __forceinline__ void prefill_tile_pp(const AttnArgs& a, int e, int b, int code, int g, int split_keys,
-                                                char* kb0, char* vb0) {
+__device__ __forceinline__ void prefill_tile_pp(const AttnArgs& a, int b, int code, int g, char* kb0, char* vb0) {
   constexpr int KB = D / 16;                        // 16-wide k blocks of the QK product
   constexpr int MB = D / 32;                        // 32-wide dim blocks of the PV product
   constexpr int SK = kKeysPerStage;                 // keys per stage
@@ -575,6 +691,7 @@ __device__ __forceinline__ void prefill_tile_pp(const AttnArgs& a, int e, int b,
   float m_run = -INFINITY, l_run = 0.f;
 
   const int n_steps = (kv_needed + SK - 1) / SK;
+  const int split_keys = (si.kind >> 4) * kKeysPerStage;
   const int n_split = tile_splits(ctx, t0, split_keys);
   const int step_begin = split * (split_keys / SK);
   const int step_end = split + 1 < n_split ? step_begin + split_keys / SK : n_steps;
@@ -872,7 +989,8 @@ __device__ __forceinline__ void prefill_tile_pp(const AttnArgs& a, int e, int b,
   // item normalises and stores bf16 O and the fp32 LSE
   const float l_tot = xor32_add(l_run);
   if (row_ok && n_split > 1) {
-    const size_t prow = (size_t)(e * H_kv + g) * kRowsPerTile + rho;
+    const int slot = a.split_base[b] + split * ((si.q_len + a.tokens_per_tile - 1) / a.tokens_per_tile) + tile;
+    const size_t prow = (size_t)(slot * H_kv + g) * kRowsPerTile + rho;
     float* po = a.part_pre_o + prow * D;
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
@@ -1258,7 +1376,6 @@ __global__ __launch_bounds__((KernelCfg<D, kKinds>::NT)) void attn_kernel(AttnAr
   __shared__ int s_item[2];
   const int n_items = a.ws_hdr[kHdrNumItems];
   const int n_pre = a.ws_hdr[kHdrNumPre];
-  const int split_keys = a.ws_hdr[kHdrPreSplitKeys];
   const int pps = a.ws_hdr[kHdrPagesPerSplit];
   const int H_kv = a.num_kv_heads;
   // Items: prefill items [0, n_pre * H_kv), decode items after them.  Prefill items are handed
@@ -1318,13 +1435,13 @@ __global__ __launch_bounds__((KernelCfg<D, kKinds>::NT)) void attn_kernel(AttnAr
         static_assert(NW == kWaves, "prefill tiles use 8 waves");
         const int2 en = a.entries[e];
         if constexpr (kKinds == 1) {
-          prefill_tile_pp<D>(a, e, en.x, en.y, g, split_keys, pk, pv);
+          prefill_tile_pp<D>(a, en.x, en.y, g, pk, pv);
         } else {
           // the mixed kernel's prefill stage buffers share its LDS region with the decode stages (a
           // workgroup runs one item at a time, and items are separated by a drained barrier)
           constexpr int B = DmaTile<D>::BYTES;
           static_assert(6 * B <= Lds<D, NW, kKinds>::bytes, "stage buffers fit the shared region");
-          prefill_tile_pp<D>(a, e, en.x, en.y, g, split_keys, smem, smem + 3 * B);
+          prefill_tile_pp<D>(a, en.x, en.y, g, smem, smem + 3 * B);
         }
       }
     } else {
@@ -1975,48 +2092,68 @@ __global__ __launch_bounds__(256) void merge_kernel(AttnArgs a, int batch) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// Merge of split prefill tiles: one wave per (job, kv-head, tile row), grid-stride over the jobs
-// the planner recorded.  Same combination as the decode merge, over the tile's splits.
+// Merge of split prefill tiles, grid-stride over the (job, kv-head, tile row) the planner recorded:
+// D / 4 lanes per row, 4 dims each, kPreMergeBlock splits in flight at a time.  Same combination as
+// the decode merge, over the tile's splits.  It reads 4 D bytes per row and split once; few loads in
+// flight per row, so several rows share a wave.
 // ------------------------------------------------------------------------------------------------
-constexpr int kMergeMaxBlocks = 4096;
+constexpr int kMergeMaxBlocks = 2048;
+constexpr int kPreMergeBlock = 4;
 
 template <int D>
 __global__ __launch_bounds__(256) void merge_prefill_kernel(AttnArgs a) {
-  if (a.ws_hdr[kHdrError] != 0) return;
-  const int lane = threadIdx.x & 63;
+  constexpr int LPR = D / 4, RPB = 256 / LPR, U = kPreMergeBlock;   // lanes per row, rows per workgroup
+  const int err = a.ws_hdr[kHdrError], jobs = a.ws_hdr[kHdrNumPreJobs];
   const int H_kv = a.num_kv_heads, H_q = a.num_q_heads, G = a.group, T = a.tokens_per_tile;
-  const int total = a.ws_hdr[kHdrNumPreJobs] * H_kv * kRowsPerTile;
-  constexpr int PER = D / 64;
-  for (int r = blockIdx.x * 4 + (threadIdx.x >> 6); r < total; r += gridDim.x * 4) {
+  const int total = err != 0 ? 0 : jobs * H_kv * kRowsPerTile;
+  const int dim = threadIdx.x % LPR * 4;
+  for (int r = blockIdx.x * RPB + threadIdx.x / LPR; r < total; r += gridDim.x * RPB) {
     const int rho = r % kRowsPerTile, jg = r / kRowsPerTile;
     const int g = jg % H_kv, j = jg / H_kv;
-    const int4 job = a.pre_jobs[j];                  // (sequence, tile, first entry, splits)
+    const int4 job = a.pre_jobs[j];                  // (sequence, tile, first slot, splits)
     const SeqInfo si = a.seqinfo[job.x];
     const int tok = job.y * T + rho / G;
     if (tok >= si.q_len) continue;
-    const int h = g * G + rho % G;
+    const int nt = (si.q_len + T - 1) / T;           // slots from one split of the tile to the next
     const int ns = job.w;
-    float M = -INFINITY;
-    for (int sp = lane; sp < ns; sp += 64)
-      M = fmaxf(M, a.part_pre_ml[2 * ((size_t)((job.z + sp) * H_kv + g) * kRowsPerTile + rho)]);
+    float M = -INFINITY, L = 0.f;
+    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int s0 = 0; s0 < ns; s0 += U) {
+      float m[U], l[U];
+      f32x4 v[U];
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
-    float acc[PER];
+      for (int u = 0; u < U; ++u) {
+        const int sp = min(s0 + u, ns - 1);          // past the end: the last split, weight 0
+        const size_t prow = (size_t)((job.z + sp * nt) * H_kv + g) * kRowsPerTile + rho;
+        m[u] = a.part_pre_ml[2 * prow];
+        l[u] = a.part_pre_ml[2 * prow + 1];
+        v[u] = *reinterpret_cast<const f32x4*>(a.part_pre_o + prow * D + dim);
+      }
+      float M_new = M;
 #pragma unroll
-    for (int i = 0; i < PER; ++i) acc[i] = 0.f;
-    float L = 0.f;
-    for (int sp = 0; sp < ns; ++sp) {
-      const size_t prow = (size_t)((job.z + sp) * H_kv + g) * kRowsPerTile + rho;
-      const float f = fexp2(a.part_pre_ml[2 * prow] - M);
-      L += f * a.part_pre_ml[2 * prow + 1];
+      for (int u = 0; u < U; ++u) M_new = fmaxf(M_new, m[u]);
+      const float alpha = s0 == 0 ? 0.f : fexp2(M - M_new);
+      L *= alpha;
 #pragma unroll
-      for (int i = 0; i < PER; ++i) acc[i] += f * a.part_pre_o[prow * D + lane * PER + i];
+      for (int i = 0; i < 4; ++i) acc[i] *= alpha;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (s0 + u >= ns) break;
+        const float f = fexp2(m[u] - M_new);
+        L += f * l[u];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i] += f * v[u][i];
+      }
+      M = M_new;
     }
     const float inv = 1.0f / L;
-    const size_t orow = (size_t)(si.q_start + tok) * H_q + h;
-#pragma unroll
-    for (int i = 0; i < PER; ++i) a.out[orow * D + lane * PER + i] = bf16_bits(acc[i] * inv);
-    if (lane == 0 && a.lse) a.lse[orow] = (M + flog2(L)) * kLn2;
+    const size_t orow = (size_t)(si.q_start + tok) * H_q + g * G + rho % G;
+    u32x2 pk;
+    pk[0] = (uint32_t)bf16_bits(acc[0] * inv) | ((uint32_t)bf16_bits(acc[1] * inv) << 16);
+    pk[1] = (uint32_t)bf16_bits(acc[2] * inv) | ((uint32_t)bf16_bits(acc[3] * inv) << 16);
+    *reinterpret_cast<u32x2*>(a.out + orow * D + dim) = pk;
+    if (dim == 0 && a.lse) a.lse[orow] = (M + flog2(L)) * kLn2;
   }
 }
 
@@ -2110,7 +2247,9 @@ int attention_grid(int head_dim, int kinds) {
 hipError_t launch_plan(const PlanParams& p, const int32_t* ctx_lens, const int32_t* cu_q_lens,
                        void* workspace, const WsLayout& lay, hipStream_t stream) {
   char* ws = static_cast<char*>(workspace);
-  hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(kPlanThreads), 0, stream, p, ctx_lens, cu_q_lens,
+  auto kernel = p.mode == kModePrefill ? plan_kernel<kModePrefill> : p.mode == kModeDecode ? plan_kernel<kModeDecode>
+                                                                                           : plan_kernel<kModeMixed>;
+  hipLaunchKernelGGL(kernel, dim3(1), dim3(kPlanThreads), 0, stream, p, ctx_lens, cu_q_lens,
                      reinterpret_cast<int32_t*>(ws + lay.hdr), reinterpret_cast<SeqInfo*>(ws + lay.seqinfo),
                      reinterpret_cast<int32_t*>(ws + lay.split_base), reinterpret_cast<int2*>(ws + lay.entries),
                      reinterpret_cast<int4*>(ws + lay.pre_jobs));
@@ -2182,8 +2321,8 @@ hipError_t launch_merge(const AttnArgs& a, int head_dim, int batch, hipStream_t 
 }
 
 hipError_t launch_merge_prefill(const AttnArgs& a, int head_dim, int64_t jobs_cap, hipStream_t stream) {
-  const int64_t waves = jobs_cap * a.num_kv_heads * kRowsPerTile;
-  int64_t grid = (waves + 3) / 4;
+  const int64_t rows = jobs_cap * a.num_kv_heads * kRowsPerTile;
+  int64_t grid = rows * (head_dim / 4) / 256;
   if (grid > kMergeMaxBlocks) grid = kMergeMaxBlocks;
   if (grid <= 0) return hipSuccess;
   if (head_dim == 64)

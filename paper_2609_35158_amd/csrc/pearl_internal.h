@@ -28,14 +28,17 @@ constexpr int kDecLongSplitPages = 128;
 // Compute units assumed when sizing decode splits (MI355X has 256).  A fixed value keeps the
 // workspace size a pure function of the shapes; the launch grid uses the device's real count.
 constexpr int kPlanComputeUnits = 256;
-// Prefill tiles are split along the keys only when the launch has few of them (at most one item
-// per compute unit); a split then holds at least kMinSplitKeys keys, and all split items of a
-// launch fit in kMaxPreSplitItems partial slots (kRowsPerTile rows each).
+// Prefill tiles are split along the keys only when the launch has few of them (the rule is at
+// plan_kernel); a split is aimed at kMinSplitKeys / 2 keys or more, the workspace is sized for
+// kMinSplitKeys, and all split items of a launch fit in kMaxPreSplitItems partial slots
+// (kRowsPerTile rows each).
 constexpr int kMinSplitKeys = 1024;
 constexpr int kMaxPreSplitItems = 2 * kPlanComputeUnits;
+// Prefill launches split tiles only up to this many tile items (tile x kv-head).
+constexpr int kPreSplitItems = 2 * kPlanComputeUnits;
 // Entry encoding of a prefill work item: y = tile | split << 16.
 constexpr int kMaxQLen = 1 << 21;        // tiles per sequence < 2^16 (>= 32 tokens per tile)
-constexpr int kMaxKvLen = 1 << 25;       // splits per tile < 2^15 (>= 1024 keys per split)
+constexpr int kMaxKvLen = 1 << 25;       // splits per tile < 2^15 (at most kMaxPreSplitItems)
 
 // XCDs (accelerator complex dies) of an MI355X, each with its own L2.
 constexpr int kNumXcd = 8;
@@ -60,7 +63,7 @@ enum Hdr : int {
   kHdrNumDec = 2,      // decode split entries
   kHdrError = 3,       // nonzero: a sequence violated the host bounds; nothing is computed
   kHdrNumItems = 4,    // (pre + dec) * H_kv
-  kHdrPreSplitKeys = 5,  // keys per prefill split (a multiple of 64); 0 = tiles are not split
+  kHdrPreSplitKeys = 5,  // keys per prefill split, at most (a multiple of 64); 0 = tiles are not split
   kHdrNumPreJobs = 6,  // prefill tiles with more than one split (merge jobs)
   // word 7: unused
   kHdrPreFirstWG = 8,  // mixed launches: workgroups [0, this) take prefill items first
@@ -75,7 +78,8 @@ struct SeqInfo {
   int32_t q_start;   // first row of the sequence in q/out
   int32_t q_len;     // new tokens
   int32_t ctx_len;   // cached tokens before the call
-  int32_t kind;      // SeqKind | (n_splits << 4) for decode sequences
+  int32_t kind;      // SeqKind | (n_splits << 4) for decode sequences, | (stages per split << 4) for
+                     // prefill ones (0: whole tiles)
 };
 
 // Offsets (bytes) of the workspace regions; all 256-byte aligned.
@@ -117,7 +121,7 @@ struct AttnArgs {
   const int2* entries;
   float* part_o;
   float* part_ml;
-  const int4* pre_jobs;      // (sequence, tile, first entry, splits) per split prefill tile
+  const int4* pre_jobs;      // (sequence, tile, first slot, splits) per split prefill tile
   float* part_pre_o;         // [slot][kRowsPerTile][D] unnormalised partial outputs
   float* part_pre_ml;        // [slot][kRowsPerTile][2] running max (log2 units) and sum
   int32_t* split_cnt;        // arrival counters, at most batch * num_kv_heads (decode planned in-kernel)

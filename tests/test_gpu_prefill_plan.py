@@ -1,0 +1,51 @@
+"""The planner's prefill entries where they can go wrong: key splits of tiles of very different
+lengths in one sequence (short tiles have fewer splits), sequences with and without splits in one
+launch, as many entries as one thread keeps and more, several chunks of sequences, and launches
+that never split.  Every row's LSE (preset to NaN) must be written; rows are compared with the
+oracle within the bf16 tolerance (1e-2 max, 1e-3 mean), rows of few keys within
+gpu_helpers.peaked_bound."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2609_35158_amd as pa
+from paper_2609_35158_amd import workloads
+from gpu_helpers import assert_close, bits, bounds, dev_lengths, gpu_append, oracle_sampled, say, tile_edge_tokens
+
+pytestmark = pytest.mark.gpu
+
+# name: (contexts, new tokens, kv-heads, G, head_dim, sequences checked)
+CASES = {
+    "one-prompt-split": ([0], [1700], 2, 2, 64, [0]),
+    "prompt-beside-long-context": ([0, 9000, 40], [900, 70, 3], 2, 4, 128, [0, 1, 2]),
+    "equal-tiles-split": ([6000, 6010], [256, 250], 4, 8, 128, [0, 1]),
+    "no-split-below-1024-keys": ([700, 0, 300], [300, 1000, 1], 1, 1, 64, [0, 1, 2]),
+    "more-entries-than-kept": ([(13 * i) % 50 for i in range(200)], [180] * 200, 1, 8, 64, [0, 7, 99, 199]),
+    "two-chunks": ([(29 * i) % 400 for i in range(260)], [1 + (7 * i) % 90 for i in range(260)], 2, 4, 64, [0, 255, 256, 259]),
+}
+
+
+@pytest.mark.parametrize("mode", ["prefill", "mixed"])
+@pytest.mark.parametrize("name", list(CASES))
+def test_prefill_entries(name, mode):
+    ctx, ql, H, G, d, seqs = CASES[name]
+    say("case: prefill plan %s (%s)" % (name, mode))
+    case = workloads.build_case(name, 91, H * G, H, d, np.array(ctx), np.array(ql), device="cuda", extra_pages=1)
+    gpu_append(case)
+    dctx, cu = dev_lengths(case)
+    max_q, max_kv = bounds(case)
+    lse = torch.full((case.total_q, case.num_q_heads), float("nan"), dtype=torch.float32, device="cuda")
+    fn = {"prefill": pa.prefill_append, "mixed": pa.mixed}[mode]
+    out, lse = fn(case.q, case.k_pool, case.v_pool, case.block_table, dctx, cu, max_q, max_kv, scale=case.scale,
+                  return_lse=True, lse=lse)
+    torch.cuda.synchronize()
+    assert torch.isfinite(lse).all(), "rows left unwritten"
+    rng = np.random.default_rng(3)
+    toks = {b: tile_edge_tokens(ql[b], 256 // G, 8, rng) for b in seqs}
+    o, l = oracle_sampled(case, seqs, toks)
+    vmax = float(case.v_new.float().abs().max().clamp(min=5.6))
+    for b in seqs:
+        rows = case.cu_q_lens[b] + np.array(toks[b])
+        assert_close(bits(out)[rows], o[b][toks[b]], lse.cpu().numpy()[rows], l[b][toks[b]],
+                     what="sequence %d" % b, peaked_vmax=vmax)
