@@ -132,8 +132,8 @@ template <int D, int NW, int kKinds> struct Lds {
 //     partial slots.  Longest first, two or three splits per unit end together; one split of the
 //     average length per unit leaves a second round of remainders: four turns of 91-392 tokens on
 //     14-23K contexts (176 items) took 367 stages on the busiest unit for an average of 228, and
-//     take 248 so (append, plan, attention and merge: 672 -> 459 us; 64-token chunks on 12-25K contexts
-//     at 4 kv-heads 236 -> 158).  With more items than kPreSplitItems whole tiles balance as well.
+//     take 248 so (append, plan, attention and merge: 672 -> 459 us).  With more items than
+//     kPreSplitItems whole tiles balance as well.
 //   * Mixed launches of up to one tile item per compute unit whose longest tile would outlast the
 //     average work per unit: split_keys is that average, at least kMinSplitKeys.  Work is estimated
 //     in key-units: a prefill tile key (256 q-rows on MFMA) costs about 3/2 of a decode key (one
@@ -642,8 +642,9 @@ template <int D, int KEYS = kKeysPerStage> struct DmaTile {
 // Before the barrier that ends phase 2j-1 every wave waits for its own copies of K(j) and V(j-1)
 // (the copies issued since stay in flight).
 // ------------------------------------------------------------------------------------------------
-template <int D>
-__device__ __forceinline__ void prefill_tile_pp(const AttnArgs& a, int b, int code, int g, char* kb0, char* vb0) {
+// at_end: called by every thread when the stages are done, before the epilogue.
+template <int D, typename AtEnd>
+__device__ __forceinline__ void prefill_tile_pp(const AttnArgs& a, int b, int code, int g, char* kb0, char* vb0, AtEnd at_end) {
   constexpr int KB = D / 16;                        // 16-wide k blocks of the QK product
   constexpr int MB = D / 32;                        // 32-wide dim blocks of the PV product
   constexpr int SK = kKeysPerStage;                 // keys per stage
@@ -985,6 +986,8 @@ __device__ __forceinline__ void prefill_tile_pp(const AttnArgs& a, int b, int co
     if (j <= n) { step(I2{}, j); ++j; }
   }
 
+
+  at_end();
   // epilogue: combine the two half-row sums; a split item stores its fp32 partial state, a whole
   // item normalises and stores bf16 O and the fp32 LSE
   const float l_tot = xor32_add(l_run);
@@ -1248,9 +1251,9 @@ __device__ __forceinline__ void decode_step(const AttnArgs& a, int p_cur, int p_
 
 // One decode item of a launch planned by plan_kernel; its partials are merged by merge_kernel after
 // the launch.
-template <int D, int NW>
+template <int D, int NW, typename AtEnd>
 __device__ __forceinline__ void decode_split(const AttnArgs& a, const DecItem& it, int pps, char* stageA,
-                                             char* stageB) {
+                                             char* stageB, AtEnd at_end) {
   constexpr int NT = NW * 64;
   using PT = PageTile<D>;
   constexpr int MB = PT::MB;
@@ -1310,6 +1313,7 @@ __device__ __forceinline__ void decode_split(const AttnArgs& a, const DecItem& i
   l_run += __shfl_xor(l_run, 16);
   l_run += __shfl_xor(l_run, 32);
 
+  at_end();
   // merge the waves' states through LDS
   __syncthreads();
   static_assert(Lds<D, NW, 2>::merge_bytes <= NW * PT::BYTES, "merge scratch fits in one set of stages");
@@ -1350,8 +1354,8 @@ __device__ __forceinline__ void decode_split(const AttnArgs& a, const DecItem& i
 }
 
 // ------------------------------------------------------------------------------------------------
-// Persistent attention kernel: workgroups pull items (entry x kv-head) from the planner's list
-// with an atomic counter (the next item is claimed while the current one runs); prefill tiles
+// Persistent attention kernel: workgroups take items (entry x kv-head) from the planner's list
+// through atomic counters (the next item is claimed as the current one ends); prefill tiles
 // come first (largest work), decode splits fill the tail.
 // ------------------------------------------------------------------------------------------------
 // kKinds: 1 = prefill tiles only, 2 = decode splits only, 3 = both (mixed batches).
@@ -1373,61 +1377,93 @@ __global__ __launch_bounds__((KernelCfg<D, kKinds>::NT)) void attn_kernel(AttnAr
   // prefill-only kernels: three K and three V stage buffers, each set contiguous
   constexpr int kDT = (kKinds == 1) ? DmaTile<D>::BYTES : 16;
   __shared__ __attribute__((aligned(16))) char pk[3 * kDT], pv[3 * kDT];
-  __shared__ int s_item[2];
+  __shared__ int s_item[2][2];                      // next item and claim mode
   const int n_items = a.ws_hdr[kHdrNumItems];
   const int n_pre = a.ws_hdr[kHdrNumPre];
   const int pps = a.ws_hdr[kHdrPagesPerSplit];
   const int H_kv = a.num_kv_heads;
-  // Items: prefill items [0, n_pre * H_kv), decode items after them.  Prefill items are handed
-  // out by the per-XCD queues below, decode items by one counter.  In mixed launches workgroups
-  // below kHdrPreFirstWG take prefill items first, the others decode items first, and each takes
-  // the other kind once its own is exhausted, so both kinds run side by side.
-  const int n_pre_items = n_pre * H_kv;
-  const bool pre_first = (int)blockIdx.x < a.ws_hdr[kHdrPreFirstWG];
+  // Items: prefill items [0, n_pre * H_kv), decode items after them.  Every workgroup's first item
+  // follows from its index: workgroups below pre_wgs (all in prefill launches, the planner's
+  // kHdrPreFirstWG in mixed ones) start with prefill items and keep to them while there are any, the
+  // others with decode items, so both kinds run side by side; each takes the other kind once its
+  // own is exhausted.  The following items are claimed at the end of the one before: claimed a whole
+  // item ahead, the longest-first order loses its balance (348 items on 256 units wait for the
+  // second of two that one unit holds: 46 stages against 34).  The claim goes out before the item's
+  // epilogue, which hides most of its latency.
+  // Before, every workgroup's first claim waited for 256 others on the counters, and at its end it
+  // asked all 8 queues one after the other while its last item waited for the answer: 28 chunks of
+  // 26 tokens on 40-80 cached ones took 47 us a call and take 24 (kernel 39 -> 17), one prompt of
+  // 2000 tokens 87 -> 72, 24 decodes beside a 256-token chunk 140 -> 129.
+  const int n_pre_items = n_pre * H_kv, n_dec_items = n_items - n_pre_items;
+  const int grid = gridDim.x;
+  const int pre_wgs = kKinds == 1 ? grid : kKinds == 2 ? 0 : min(a.ws_hdr[kHdrPreFirstWG], grid);
+  const int dec_wgs = grid - pre_wgs;
+  const bool pre_first = (int)blockIdx.x < pre_wgs;
   // Prefill items: item i belongs to queue i % 8, and a workgroup takes the items of the queue of
   // the XCD it runs on, then those of the other queues in turn.  With 8 kv-heads the items of
   // one (sequence, kv-head) then share one XCD's L2 (with 4, two XCDs): every tile of a sequence
   // re-reads that head's whole context, which other XCDs would each fetch from memory again.  The
   // queues are balanced (the heads of a tile are equal work), and the turn to other queues
-  // completes every item wherever the workgroups run.
-  int queue = xcc_id(), queues_left = kNumXcd;      // thread 0's claim state
-  auto claim_pre = [&](int limit) -> int {          // a prefill item below limit, or -1
-    while (queues_left > 0) {
-      const int c = atomicAdd(&a.ws_hdr[kHdrQueues + queue], 1);
-      const int64_t i = queue + (int64_t)kNumXcd * c;
-      if (i < limit) return (int)i;
-      queue = (queue + 1) % kNumXcd;
-      --queues_left;
-    }
-    return -1;
+  // completes every item wherever the workgroups run.  Claim c of queue q is its item after those
+  // the workgroups started with.
+  auto pre_item = [&](int q, int c) { return (unsigned)q + kNumXcd * (unsigned)(c + ((pre_wgs - q + kNumXcd - 1) >> 3)); };
+  static_assert(kNumXcd == 8, "queue arithmetic");
+  const int xcd = xcc_id();
+  // What the next claim tries: 0 nothing (every item is some workgroup's first one), 1 this XCD's
+  // prefill queue, 2 the decode counter.
+  const bool any_pre = (kKinds & 1) && n_pre_items > pre_wgs, any_dec = (kKinds & 2) && n_dec_items > dec_wgs;
+  int mode = pre_first ? (any_pre ? 1 : any_dec ? 2 : 0) : (any_dec ? 2 : any_pre ? 1 : 0);
+  int claimed = 0;                                  // thread 0's
+  auto send_claim = [&]() {
+    if (mode != 0 && threadIdx.x == 0) claimed = atomicAdd(&a.ws_hdr[mode == 1 ? kHdrQueues + xcd : kHdrCounter], 1);
   };
-  auto claim = [&]() -> int {
-    if constexpr (kKinds == 1) {
-      const int i = claim_pre(n_items);
-      return i >= 0 ? i : n_items;
-    } else if constexpr (kKinds == 2) {
-      return atomicAdd(&a.ws_hdr[kHdrCounter], 1);
-    } else {
-      const int n_dec_items = n_items - n_pre_items;
-      if (pre_first) {
-        const int c = claim_pre(n_pre_items);
-        if (c >= 0) return c;
-        const int d = atomicAdd(&a.ws_hdr[kHdrCounter], 1);
-        return d < n_dec_items ? n_pre_items + d : n_items;
-      } else {
-        const int d = atomicAdd(&a.ws_hdr[kHdrCounter], 1);
-        if (d < n_dec_items) return n_pre_items + d;
-        const int c = claim_pre(n_pre_items);
-        return c >= 0 ? c : n_items;
+  // Wave 0, after send_claim: the next item (-1: none left) to s_item[slot], the next mode beside it.
+  // If the tried kind is exhausted here, one read of all queue counters finds a queue that still
+  // holds items, so an exhausted launch costs one round trip and not one per queue.
+  auto take_claim = [&](int slot) {
+    const int c = __builtin_amdgcn_readfirstlane(claimed), lane = threadIdx.x;
+    int next = -1, next_mode = mode;
+    if (mode == 1) {
+      if (pre_item(xcd, c) < (unsigned)n_pre_items) next = (int)pre_item(xcd, c);
+    } else if (dec_wgs + c < n_dec_items) {
+      next = n_pre_items + dec_wgs + c;
+    }
+    for (int tries = 0; tries < 2 && next < 0; ++tries) {   // the other queues, or the other kind
+      if (any_pre && (mode == 1) == (tries == 0)) {
+        for (;;) {
+          const int n = __hip_atomic_load(&a.ws_hdr[kHdrQueues + (lane & 7)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          const unsigned has = (unsigned)__ballot(lane < kNumXcd && pre_item(lane, n) < (unsigned)n_pre_items);
+          if (!has) break;
+          const int q = (xcd + __builtin_ctz((has >> xcd) | (has << (kNumXcd - xcd)))) & 7;   // own queue first
+          int got = 0;
+          if (lane == 0) got = atomicAdd(&a.ws_hdr[kHdrQueues + q], 1);
+          const unsigned i = pre_item(q, __builtin_amdgcn_readfirstlane(got));
+          if (i < (unsigned)n_pre_items) { next = (int)i; next_mode = 1; break; }   // else taken meanwhile
+        }
+      } else if (any_dec && mode == 1) {
+        int got = 0;
+        if (lane == 0) got = atomicAdd(&a.ws_hdr[kHdrCounter], 1);
+        got = dec_wgs + __builtin_amdgcn_readfirstlane(got);
+        if (got < n_dec_items) { next = n_pre_items + got; next_mode = 2; }
       }
     }
+    if (lane == 0) { s_item[slot][0] = next; s_item[slot][1] = next_mode; }
   };
-  if (threadIdx.x == 0) s_item[0] = claim();
-  __syncthreads();
+  int item = pre_first ? ((int)blockIdx.x < n_pre_items ? (int)blockIdx.x : -1)
+                       : ((int)blockIdx.x - pre_wgs < n_dec_items ? n_pre_items + (int)blockIdx.x - pre_wgs : -1);
   int slot = 0;
-  int item = s_item[0];
-  while (item < n_items) {
-    if (threadIdx.x == 0) s_item[slot ^ 1] = claim();
+  auto go_on = [&]() {                              // after send_claim, by all threads
+    if (threadIdx.x < 64) take_claim(slot);
+    __syncthreads();
+    item = __builtin_amdgcn_readfirstlane(s_item[slot][0]);
+    mode = __builtin_amdgcn_readfirstlane(s_item[slot][1]);
+    slot ^= 1;
+  };
+  if (item < 0 && mode != 0) {                      // none of the own kind to start with
+    send_claim();
+    go_on();
+  }
+  while (item >= 0) {
     const int e = item / H_kv;
     const int g = item - e * H_kv;
     if (e < n_pre) {
@@ -1435,13 +1471,13 @@ __global__ __launch_bounds__((KernelCfg<D, kKinds>::NT)) void attn_kernel(AttnAr
         static_assert(NW == kWaves, "prefill tiles use 8 waves");
         const int2 en = a.entries[e];
         if constexpr (kKinds == 1) {
-          prefill_tile_pp<D>(a, en.x, en.y, g, pk, pv);
+          prefill_tile_pp<D>(a, en.x, en.y, g, pk, pv, send_claim);
         } else {
           // the mixed kernel's prefill stage buffers share its LDS region with the decode stages (a
           // workgroup runs one item at a time, and items are separated by a drained barrier)
           constexpr int B = DmaTile<D>::BYTES;
           static_assert(6 * B <= Lds<D, NW, kKinds>::bytes, "stage buffers fit the shared region");
-          prefill_tile_pp<D>(a, en.x, en.y, g, smem, smem + 3 * B);
+          prefill_tile_pp<D>(a, en.x, en.y, g, smem, smem + 3 * B, send_claim);
         }
       }
     } else {
@@ -1449,12 +1485,11 @@ __global__ __launch_bounds__((KernelCfg<D, kKinds>::NT)) void attn_kernel(AttnAr
         const int2 en = a.entries[max_pre + (e - n_pre)];
         const SeqInfo si = a.seqinfo[en.x];
         const DecItem it{en.x, en.y, g, si.q_start, si.ctx_len + si.q_len, si.kind >> 4, a.split_base[en.x]};
-        decode_split<D, NW>(a, it, pps, stageA, stageB);
+        decode_split<D, NW>(a, it, pps, stageA, stageB, send_claim);
       }
     }
-    __syncthreads();
-    slot ^= 1;
-    item = s_item[slot];
+    if (mode == 0) break;
+    go_on();
   }
 }
 
