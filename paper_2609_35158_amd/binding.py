@@ -144,8 +144,15 @@ def _need(t: torch.Tensor, name: str, dtype: torch.dtype) -> None:
         raise ValueError("%s must be contiguous" % name)
 
 
+# The raw handle of torch's current stream: building the Stream object that
+# torch.cuda.current_stream() returns takes 2.7 us, a fifth of a small decode step's host time.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def make_shape(num_q_heads: int, k_pool: torch.Tensor) -> KvShape:
