@@ -1742,15 +1742,17 @@ __device__ __forceinline__ void ld_dev2(const float* p, float& x, float& y) {
 
 // Merge of a cut pair (kv-head g) from its partials, in the workgroup that counted itself in last:
 //   o = sum_s 2^(m_s - m*) o~_s / sum_s 2^(m_s - m*) l_s,   lse = (m* + log2 l*) ln 2.
-// A lane takes D/16 dims of a q-head and the (m, l) of that head (4 heads a pass), kMergeBlock
-// partials in flight at a time.
-constexpr int kMergeBlock = 8;
+// A lane takes D/16 dims of a q-head and the (m, l) of that head (4 heads a pass), up to kMergeBlock
+// partials in flight at a time and no load beyond the pair's own (one sequence of 2732 keys, 10
+// partials a pair: 13.8 us a call with blocks of 8, 13.15 with 12, 13.2 with 16; with the last
+// partial loaded again to fill every block, 512 sequences of 2-3 partials took 195-200 us, now 190).
+constexpr int kMergeBlock = 12;
 
 template <int D>
 __device__ __forceinline__ void merge_pair(const AttnArgs& a, const CutPair& c, int g, int stride, int max_dec, int pass) {
   constexpr int U = kMergeBlock, PER = D / 16;
   const int G = a.group, H_q = a.num_q_heads;
-  const int ns = c.n;
+  const int ns = uni(c.n);
   const int lane = threadIdx.x & 63, head = 4 * pass + lane / 16, dim = lane % 16 * PER;
   if (head >= G) return;
   float M = -INFINITY, L = 0.f, acc[PER];
@@ -1761,11 +1763,14 @@ __device__ __forceinline__ void merge_pair(const AttnArgs& a, const CutPair& c, 
     float v[U][PER], m[U], l[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int s = min(s0 + u, ns - 1);            // past the end: the last partial, weight 0
-      const size_t slot = ((size_t)g * max_dec + (s == 0 ? c.slot0 : stride * (c.x0 + s))) * G + head;
-      ld_dev2(&a.part_ml[2 * slot], m[u], l[u]);
+      m[u] = -INFINITY;
+      if (s0 + u < ns) {                            // uniform
+        const int s = s0 + u;
+        const size_t slot = ((size_t)g * max_dec + (s == 0 ? c.slot0 : stride * (c.x0 + s))) * G + head;
+        ld_dev2(&a.part_ml[2 * slot], m[u], l[u]);
 #pragma unroll
-      for (int i = 0; i < PER; i += 2) ld_dev2(&a.part_o[slot * D + dim + i], v[u][i], v[u][i + 1]);
+        for (int i = 0; i < PER; i += 2) ld_dev2(&a.part_o[slot * D + dim + i], v[u][i], v[u][i + 1]);
+      }
     }
     float M_new = M;
 #pragma unroll
@@ -1776,11 +1781,12 @@ __device__ __forceinline__ void merge_pair(const AttnArgs& a, const CutPair& c, 
     for (int i = 0; i < PER; ++i) acc[i] *= alpha;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      if (s0 + u >= ns) break;
-      const float f = fexp2(m[u] - M_new);
-      L += f * l[u];
+      if (s0 + u < ns) {                            // uniform
+        const float f = fexp2(m[u] - M_new);
+        L += f * l[u];
 #pragma unroll
-      for (int i = 0; i < PER; ++i) acc[i] += f * v[u][i];
+        for (int i = 0; i < PER; ++i) acc[i] += f * v[u][i];
+      }
     }
     M = M_new;
   }
