@@ -1695,7 +1695,10 @@ struct DecShares {
       n_runs = d.runs_heads;
     } else {
       heads = 1;
-      n_runs = max(1, min(d.runs_one, pages / kDecMinPages));
+      // Long sequences in few pairs take somewhat longer runs, so that a pair is not merged from 100
+      // pieces: three of 5-20K tokens on one kv-head 22.0 us a call with kDecMinPages alone, 19.4 so.
+      const int least = kDecMinPages + (int)((unsigned)pages / (64u * (unsigned)d.batch));
+      n_runs = max(1, min(d.runs_one, pages / least));
     }
     const int n = n_runs * subs();
     len = (int)((unsigned)pages / (unsigned)n);
@@ -1827,7 +1830,21 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 4 : 2) void decode_kernel(AttnA
     if (blockIdx.x == 0 && threadIdx.x == 0) a.ws_hdr[kHdrError] = 1;
     return;
   }
-  const DecShares sh(total_pages, d);
+  DecShares sh(total_pages, d);
+  // A few sequences not much longer than a run: a workgroup per (sequence, kv-head) instead of equal
+  // runs, so that no pair is cut between workgroups (the acknowledged stores, the count-in and the
+  // merge take about as long as 3 more pages a wave; us a call with equal runs and so, 32 q-heads:
+  // 4 of 200-400 tokens at 2 kv-heads 14.1 and 11.8; 24 of 500-1000 at 8 21.1 and 19.2; but one of
+  // 770 at 4, 30 pages over its run, 11.6 and 13.0).
+  bool whole_pairs = false;
+  if (B <= 64 && B * H <= (int)gridDim.x && sh.heads == 1) {
+    const int i = min((int)threadIdx.x & 63, B - 1), most = total_pages / sh.n_runs + kDecWholePages;
+    whole_pairs = !__any(P.pre[i + 1] - P.pre[i] > most);
+  }
+  if (whole_pairs) {
+    sh.heads = 1;
+    sh.n_runs = B;
+  }
   const int n_blk = H / sh.heads;                   // head blocks
   if ((int)blockIdx.x >= sh.n_runs * n_blk) return;
   // Run x of a head block is workgroup x n_blk + (block - x) mod n_blk: the blocks of a run start
@@ -1835,8 +1852,18 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 4 : 2) void decode_kernel(AttnA
   const int x = blockIdx.x / n_blk;
   const int g0 = (blockIdx.x + x) % n_blk * sh.heads;
   const int sub = w / sh.heads, g = g0 + w % sh.heads;
-  const int share = x * sh.subs() + sub;
-  const int t0 = sh.begin(share), n = sh.begin(share + 1) - t0;
+  int run0, t0, n;                                  // the run's first entry; the wave's share
+  if (whole_pairs) {
+    run0 = uni(P.pre[x]);
+    const int len = uni(P.pre[x + 1]) - run0, q = len / NW, r = len % NW;
+    t0 = run0 + w * q + min(w, r);
+    n = q + (w < r);
+  } else {
+    const int share = x * sh.subs() + sub;
+    run0 = sh.begin(x * sh.subs());
+    t0 = sh.begin(share);
+    n = sh.begin(share + 1) - t0;
+  }
   // partial slots and counters of a kv-head: two slots and a counter per run, or a slot per run,
   // and a slot and a counter per sequence, if that is fewer
   const bool per_pair = B < sh.n_runs;
@@ -2031,7 +2058,6 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 4 : 2) void decode_kernel(AttnA
     // bits 0..7: chains that start with share q's last pair; bit 8: the first share's first pair
     unsigned todo = (unsigned)__ballot(lane < subs && e.last_b >= 0 && (!e.before || lane == 0)) |
                     ((has_first & 1u) << NW);
-    const int run0 = sh.begin(x * subs);
     const int rows = sh.heads * G;                  // q-heads of the workgroup
     while (todo) {
       const int q0 = __builtin_ctz(todo);

@@ -50,6 +50,9 @@ constexpr int kDecPlanMaxSeqs = 1024;
 // several kv-heads share a workgroup if its waves' shares hold kDecHeadPages pages or more.
 constexpr int kDecMinPages = 16;
 constexpr int kDecHeadPages = 64;
+// Up to 64 sequences of at most kDecWholePages pages more than a run are not cut if there is a
+// workgroup for every (sequence, kv-head) pair.
+constexpr int kDecWholePages = 28;
 
 enum Mode : int { kModePrefill = 0, kModeDecode = 1, kModeMixed = 2 };
 

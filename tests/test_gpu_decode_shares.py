@@ -1,6 +1,6 @@
 """The equal-share decode kernel where its cuts can go wrong: fewer pages than waves, pairs that end
 exactly at a share's or a workgroup's boundary, one pair cut by many workgroups, many pairs per
-share, kv-head counts that do not divide the grid, both plan forms (up to 64 sequences and more),
+share, a few short sequences that are not cut at all, kv-head counts that do not divide the grid, both plan forms (up to 64 sequences and more),
 and workgroups of several kv-heads.  Each case goes through pearl_attn_decode_append (pools compared
 byte for byte) and against the oracle.  Many sequences here hold only a few keys, so single weights
 dominate their rows; the bound is the one gpu_helpers.peaked_bound derives for that from the bf16
@@ -26,6 +26,9 @@ CASES = {
     "64-sequences": ([(11 * i) % 70 for i in range(64)], 5, 1, 128),
     "cuts-at-pair-ends": ([16 * 16 - 1] * 48, 8, 4, 128),
     "cuts-at-pair-ends-d64": ([16 * 8 - 1] * 64, 4, 8, 64),
+    "whole-pairs": ([300, 0, 17, 410, 1, 255, 256], 8, 4, 128),
+    "whole-pairs-d64": ([50 * i for i in range(20)], 3, 8, 64),
+    "one-too-long-for-whole-pairs": ([900, 100, 90], 2, 2, 128),
     "one-long": ([30011], 2, 8, 128),
     "long-beside-short": ([20000, 3, 17, 9000, 1], 4, 2, 64),
     "many-pairs-per-share": ([(37 * i) % 90 for i in range(520)], 8, 1, 64),
