@@ -1562,10 +1562,10 @@ __global__ __launch_bounds__((KernelCfg<D, kKinds>::NT)) void attn_kernel(AttnAr
 // store acknowledgement, the count-in and the last merge (5-8 us).  Before, splits of equal size
 // came from a work queue and each drained its pipeline and merged 8 waves (3.6 us per split, and a
 // tail of a split's length).  Times of a call, before and now (32 q-heads, d = 128 unless said;
-// same card, in turn): 64 sequences of 2K-16K tokens, 8 kv-heads 361 -> 355 us; 256 around 6K
-// tokens, 4 kv-heads 646 -> 636; 512 of 64-1024 tokens 202 -> 195; 32 around 6K, 4 kv-heads
-// 93.3 -> 84.2; 48 of 500-6000 tokens, 16 q-heads, 8 kv-heads, d = 64 60.7 -> 55.2; one of 16000
-// tokens 34.1 -> 22.1; 200 of 40-160 tokens 37.4 -> 26.7.
+// same card, in turn): 64 sequences of 2K-16K tokens, 8 kv-heads 361 -> 352 us; 256 around 6K
+// tokens, 4 kv-heads 647 -> 634; 512 of 64-1024 tokens 202 -> 190; 32 around 6K, 4 kv-heads
+// 93.1 -> 82.7; 48 of 500-6000 tokens, 16 q-heads, 8 kv-heads, d = 64 60.9 -> 55.1; one of 2731
+// tokens 14.6 -> 13.2, of 16000 34.1 -> 21.5; 200 of 40-160 tokens 37.4 -> 26.4.
 // The shares follow from the lengths alone, so results do not depend on timing.  Every workgroup
 // finds its place by itself from the prefix sums of the pages per sequence (decode_plan), so the
 // call is a zeroing launch and this kernel.
