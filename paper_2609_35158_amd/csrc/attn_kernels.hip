@@ -1594,7 +1594,8 @@ __device__ __forceinline__ bool dec_seq(const AttnArgs& a, const DecPlanArgs& d,
 
 // Builds the prefix sums; returns the total pages, or -1 if a length violates the host bounds.
 // Batches of at most 64 sequences: every wave builds the same list (the same values to the same
-// words), a lane per sequence, so no barrier is needed.
+// words), a lane per sequence, so no barrier is needed; a wave reads other lanes' words only after
+// the fence that orders its own stores before them.
 __device__ __forceinline__ int decode_plan(const AttnArgs& a, const DecPlanArgs& d, DecPlanLds& P) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, B = d.batch;
   auto wave_scan = [&](int v) {
@@ -1614,6 +1615,9 @@ __device__ __forceinline__ int decode_plan(const AttnArgs& a, const DecPlanArgs&
       P.tail[lane] = (unsigned char)tail;
     }
     if (lane == 0) P.pre[0] = 0;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     const int total = __shfl(incl, 63);
     return __any(bad) ? -1 : total;
   }

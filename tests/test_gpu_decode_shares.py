@@ -13,7 +13,7 @@ import torch
 import oracle
 import paper_2609_35158_amd as pa
 from paper_2609_35158_amd import workloads
-from gpu_helpers import assert_close, bits, oracle_sampled, say
+from gpu_helpers import assert_close, bits, gpu_append, oracle_sampled, say
 
 pytestmark = pytest.mark.gpu
 
@@ -76,3 +76,30 @@ def test_several_heads_per_workgroup(H, G, d):
     o, l = oracle_sampled(case, seqs)
     for b in seqs:
         assert_close(bits(out[b:b + 1]), o[b], lse[b:b + 1].cpu().numpy(), l[b], what="sequence %d" % b)
+
+
+@pytest.mark.parametrize("batch", [2, 31, 33, 64])
+def test_plan_of_one_wave(batch):
+    """Up to 64 sequences each wave builds the page list alone, a lane per sequence, and then reads the
+    other lanes' entries: a sequence's results must be the ones it gets in a batch of more, which is
+    planned behind barriers."""
+    say("case: decode shares, plan of one wave, %d sequences" % batch)
+    rng = np.random.default_rng(70 + batch)
+    ctx = rng.integers(0, 400, size=70)
+    ctx[:batch] += 16 * rng.integers(0, 60, size=batch)
+    case = workloads.build_case("one-wave", 79, 8, 2, 64, ctx, np.ones(70, np.int64), device="cuda", sentinel_unused=False)
+    gpu_append(case)
+    lens = torch.from_numpy(case.ctx_lens.astype(np.int32)).cuda()
+    max_kv = int(case.kv_lens.max())
+    args = lambda n: (case.q[:n], case.k_pool, case.v_pool, case.block_table[:n], lens[:n], max_kv)
+    few, lse_few = pa.decode(*args(batch), scale=case.scale, return_lse=True)
+    more, lse_more = pa.decode(*args(70), scale=case.scale, return_lse=True)
+    torch.cuda.synchronize()
+    # two cuts of the same sequence: each within the tolerance of the exact result
+    assert (few.float() - more[:batch].float()).abs().max().item() <= 2e-2
+    assert (lse_few - lse_more[:batch]).abs().max().item() <= 1e-3
+    seqs = sorted({0, batch // 2, batch - 1})
+    o, l = oracle_sampled(case, seqs)
+    for b in seqs:
+        assert_close(bits(few[b:b + 1]), o[b], lse_few[b:b + 1].cpu().numpy(), l[b], what="sequence %d" % b,
+                     peaked_vmax=float(case.v_new.float().abs().max().clamp(min=5.6)))
