@@ -282,7 +282,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(
   }
   if (bad) {
     if (tid == 0) {
-      hdr[kHdrCounter] = 0; hdr[kHdrNumPre] = 0; hdr[kHdrNumDec] = 0;
+      hdr[kHdrCounter] = 0; hdr[kHdrNumPre] = 0; hdr[kHdrNumDec] = 0; hdr[kHdrPreFirstWG] = 0;
       hdr[kHdrError] = 1; hdr[kHdrNumItems] = 0; hdr[kHdrPreSplitKeys] = 0; hdr[kHdrNumPreJobs] = 0;
       hdr[kHdrPagesPerSplit] = p.pages_per_split;
     }

@@ -49,3 +49,24 @@ def test_prefill_entries(name, mode):
         rows = case.cu_q_lens[b] + np.array(toks[b])
         assert_close(bits(out)[rows], o[b][toks[b]], lse.cpu().numpy()[rows], l[b][toks[b]],
                      what="sequence %d" % b, peaked_vmax=vmax)
+
+
+@pytest.mark.parametrize("mode", ["prefill", "mixed"])
+def test_refused_launch_leaves_no_stale_header(mode):
+    """A length beyond the host bounds: nothing is computed, and every header word that the attention
+    kernel reads is written, whatever the workspace held before."""
+    from paper_2609_35158_amd import binding as bd
+    say("case: refused %s launch" % mode)
+    case = workloads.build_case("refused", 92, 8, 2, 64, np.array([100, 40, 7]), np.array([30, 1, 1]), device="cuda")
+    gpu_append(case)
+    dctx, cu = dev_lengths(case)
+    max_q, _ = bounds(case)
+    desc = bd.make_desc(case.block_table, dctx, cu, case.total_q, max_q, 64)   # the first sequence holds 130 keys
+    ws = torch.full((bd.workspace_bytes(case.num_q_heads, case.k_pool, desc),), 0x7f, dtype=torch.uint8, device="cuda")
+    out = torch.full_like(case.q, 7.0)
+    fn = {"prefill": pa.prefill_append, "mixed": pa.mixed}[mode]
+    fn(case.q, case.k_pool, case.v_pool, case.block_table, dctx, cu, max_q, 64, scale=case.scale, out=out, workspace=ws)
+    torch.cuda.synchronize()
+    hdr = ws[:64 * 4].view(torch.int32).cpu().numpy()
+    assert hdr[3] == 1 and not hdr[[0, 1, 2, 4, 5, 6, 8]].any() and not hdr[16:24].any() and 0 < hdr[9] < 1 << 20
+    assert torch.all(out == 7.0)
