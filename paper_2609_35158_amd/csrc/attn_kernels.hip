@@ -1212,7 +1212,13 @@ __device__ __forceinline__ void issue_whole_or_last(const AttnArgs& a, int phys,
 }
 
 // Attends the G heads to logical page p staged at buf, updating the wave's online softmax state.
-template <int D>
+// kFine: the weights enter P.V as two bf16 parts, the upper 8 significant bits (cut off, so the rest
+// is >= 0) and the rest, side by side in the k dimension of one 16x16x32 product (the keys twice).
+// Rounded to bf16 once, a weight is off by up to 2^-9 unless it is the largest of its run, which is
+// exactly 1: the fewer runs a sequence is cut into, the larger the error, and the equal shares'
+// long runs took the error of 64 sequences of 2K-16K tokens from 0.00179 to 0.00187 (2-norm, against
+// 64 bits); in two parts it is 0.00166, that of rounding the exact result to bf16.
+template <int D, bool kFine>
 __device__ __forceinline__ void decode_consume(int p, int kv, const bf16x8* qop, f32x4* oacc, float& m_run,
                                                float& l_run, const float c, const char* buf) {
   using PT = PageTile<D>;
@@ -1236,13 +1242,20 @@ __device__ __forceinline__ void decode_consume(int p, int kv, const bf16x8* qop,
   const bool grow = mx * c > m_run;
   const float m_new = grow ? mx * c : m_run;
   const float alpha = grow ? fexp2(m_run - m_new) : 1.0f;
-  i16x4 pop;
+  i16x4 pop, rest;
   float psum = 0.f;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const float pr = fexp2(__builtin_fmaf(sc[r], c, -m_new));
     psum += pr;
-    pop[r] = (short)bf16_bits(pr);
+    if constexpr (kFine) {
+      const unsigned upper = __builtin_bit_cast(unsigned, pr) & 0xffff0000u;
+      pop[r] = (short)(upper >> 16);
+      // never 0 unless the weight is, so an infinite V stays infinite (0 times it would be NaN)
+      rest[r] = (short)bf16_bits(fmaxf(pr - __builtin_bit_cast(float, upper), fminf(pr, 0x1p-100f)));
+    } else {
+      pop[r] = (short)bf16_bits(pr);
+    }
   }
   l_run = l_run * alpha + psum;
   if (__ballot(grow)) {
@@ -1256,7 +1269,10 @@ __device__ __forceinline__ void decode_consume(int p, int kv, const bf16x8* qop,
 #pragma unroll
   for (int mb = 0; mb < PT::MB; ++mb) {
     const i16x4 v = lds_read_tr(buf, PT::voff(r0, 16 * mb + 4 * (j & 3)));
-    oacc[mb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(v, pop, oacc[mb], 0, 0, 0);
+    if constexpr (kFine)
+      oacc[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(concat_tr(v, v), concat_tr(pop, rest), oacc[mb], 0, 0, 0);
+    else
+      oacc[mb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(v, pop, oacc[mb], 0, 0, 0);
   }
 }
 
@@ -1292,7 +1308,7 @@ __device__ __forceinline__ void decode_step(const AttnArgs& a, int p_cur, int p_
   } else {
     __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
   }
-  decode_consume<D>(p_cur, kv, qop, oacc, m_run, l_run, a.scale_log2, s_cur);
+  decode_consume<D, false>(p_cur, kv, qop, oacc, m_run, l_run, a.scale_log2, s_cur);
 }
 
 // One decode item of a launch planned by plan_kernel; its partials are merged by merge_kernel after
@@ -1971,7 +1987,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 4 : 2) void decode_kernel(AttnA
         l_run = 0.f;
         whole = cur.p == 0;
       }
-      decode_consume<D>(cur.p, cur.kv, qop, oacc, m_run, l_run, a.scale_log2, st + buf);
+      decode_consume<D, true>(cur.p, cur.kv, qop, oacc, m_run, l_run, a.scale_log2, st + buf);
       const bool ends_here = cur.p == cur.np - 1;
       if (ends_here && a.k_new) {
         // the new token's row goes into the pools from the stage (no wave reads it from there; a
