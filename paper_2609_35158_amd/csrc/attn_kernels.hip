@@ -1594,6 +1594,7 @@ struct DecPlanLds {
   unsigned char tail[kDecPlanMaxSeqs];     // (attended keys - 1) % kPage
   int wsum[kWaves];
   int err;
+  int over;                                // a sequence is longer than all_within's limit
 };
 
 __device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
@@ -1609,10 +1610,11 @@ __device__ __forceinline__ bool dec_seq(const AttnArgs& a, const DecPlanArgs& d,
 }
 
 // Builds the prefix sums; returns the total pages, or -1 if a length violates the host bounds.
+// most: the most pages of this thread's sequences (of this lane's: every wave holds them all).
 // Batches of at most 64 sequences: every wave builds the same list (the same values to the same
 // words), a lane per sequence, so no barrier is needed; a wave reads other lanes' words only after
 // the fence that orders its own stores before them.
-__device__ __forceinline__ int decode_plan(const AttnArgs& a, const DecPlanArgs& d, DecPlanLds& P) {
+__device__ __forceinline__ int decode_plan(const AttnArgs& a, const DecPlanArgs& d, DecPlanLds& P, int& most) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, B = d.batch;
   auto wave_scan = [&](int v) {
 #pragma unroll
@@ -1635,17 +1637,20 @@ __device__ __forceinline__ int decode_plan(const AttnArgs& a, const DecPlanArgs&
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     const int total = __shfl(incl, 63);
+    most = pages;
     return __any(bad) ? -1 : total;
   }
-  if (tid == 0) { P.err = 0; P.pre[0] = 0; }
+  if (tid == 0) { P.err = 0; P.pre[0] = 0; P.over = 0; }
   __syncthreads();
   int carry = 0;
+  most = 0;
 #pragma unroll
   for (int c = 0; c < kDecPlanChunks; ++c) {
     if (c * kThreads >= B) break;                   // uniform
     const int b = c * kThreads + tid;
     int pages = 0, tail = 0;
     const bool bad = b < B && !dec_seq(a, d, b, pages, tail);
+    most = max(most, pages);
     const int incl = wave_scan(pages);
     if (lane == 63) P.wsum[wv] = incl;
     if (__any(bad) && lane == 0) P.err = 1;
@@ -1698,19 +1703,36 @@ __device__ __forceinline__ void advance(const DecPlanLds& P, PageCursor& c) {
   c.kv = (c.np - 1) * kPage + uni(P.tail[c.b]) + 1;
 }
 
+// Whether no sequence holds more than `limit` pages, `most` being decode_plan's: called once, by all
+// threads.
+__device__ __forceinline__ bool all_within(DecPlanLds& P, int B, int most, int limit) {
+  const bool over = __any(most > limit);
+  if (B <= 64) return !over;
+  if (over && (threadIdx.x & 63) == 0) P.over = 1;
+  __syncthreads();
+  return P.over == 0;
+}
+
 // The cut of the page list.  A workgroup takes `heads` kv-heads (a power of two up to 8 that
 // divides H) and one of n_runs runs of 8 / heads consecutive shares; the first `more` shares hold
 // len + 1 entries, the others len.  Several heads per workgroup read the adjacent blocks of a page
-// together, which HBM serves faster: 64 sequences of 2K-16K tokens take 355 us so and 363 us with
-// one head per workgroup.  But then every share's end cuts a pair between workgroups, and a pair
-// of many short shares is slow to merge: 32 sequences around 6K tokens (29 pages per share, the
-// longest pair in 36 pieces) take 104 us so and 84 us with one head.  So workgroups take several
-// heads only if a share holds at least kDecHeadPages pages (measured on both sides at 29 and 69
-// pages per share: 104 against 84 us, and 194 against 197 us).
+// together, which HBM serves faster (2% of a share's time at 8 heads, 9% at 64).  But then every
+// share's end cuts a pair between workgroups, and the last merges take longer the more pieces a pair
+// is cut into.  So workgroups take several heads if the longest pair's pieces, longest / len, are few
+// for the share's length: kDecPieceCost * longest / len <= len.  Measured (us a call with one head
+// and with several; G = 4, G = 1 above 16 kv-heads; pages per share, pieces of the longest pair):
+//   several are faster: 64 sequences of 2K-16K tokens, 8 kv-heads (144, 7) 363 and 355; 32 of 400-1600,
+//     64 kv-heads (62, 1.6) 178 and 163; the same at 40 (39, 2.6) 110 and 107; 64 of 100-400, 64 kv-heads
+//     (31, 1) 95.8 and 89.1; 256 of 1K-8K, 2 kv-heads (70, 7) 191 and 186;
+//   one is faster: 48 of 2K-6K, 8 kv-heads (47, 8) 124 and 130; 32 of them (31, 12) 87 and 100; 16 of
+//     2K-30K (64, 29) 171 and 188; 8 of 4K-16K, 16 kv-heads (39, 25) 116 and 135; 32 of 500-2000, 16
+//     kv-heads (19, 6) 59 and 66; 200 of 500-2000, 4 kv-heads (30, 4) 89.5 and 90.1.
 struct DecShares {
   int heads, n_runs, len, more;
-  __device__ __forceinline__ DecShares(int pages, const DecPlanArgs& d) {
-    if (d.heads > 1 && pages >= kDecHeadPages * kWaves / d.heads * d.runs_heads) {
+  __device__ __forceinline__ DecShares(DecPlanLds& P, int pages, int most, const DecPlanArgs& d) {
+    const int len_heads = d.heads > 1 ? (int)((unsigned)pages / (unsigned)(kWaves / d.heads * d.runs_heads)) : 0;
+    const int longest = min(len_heads, 1 << 15) * min(len_heads, 1 << 15) / kDecPieceCost;   // at most
+    if (d.heads > 1 && (unsigned)pages <= (unsigned)longest * (unsigned long long)d.batch && all_within(P, d.batch, most, longest)) {
       heads = d.heads;
       n_runs = d.runs_heads;
     } else {
@@ -1845,12 +1867,13 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 4 : 2) void decode_kernel(AttnA
   const int G = a.group, H = a.num_kv_heads, H_q = a.num_q_heads, B = d.batch;
   const bool head_ok = hh < G;
 
-  const int total_pages = uni(decode_plan(a, d, P));
+  int most;
+  const int total_pages = uni(decode_plan(a, d, P, most));
   if (total_pages < 0) {                            // the prologue cleared the error flag
     if (blockIdx.x == 0 && threadIdx.x == 0) a.ws_hdr[kHdrError] = 1;
     return;
   }
-  DecShares sh(total_pages, d);
+  DecShares sh(P, total_pages, most, d);
   // A few sequences not much longer than a run: a workgroup per (sequence, kv-head) instead of equal
   // runs, so that no pair is cut between workgroups (the acknowledged stores, the count-in and the
   // merge take about as long as 3 more pages a wave; us a call with equal runs and so, 32 q-heads:

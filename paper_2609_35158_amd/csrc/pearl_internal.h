@@ -47,9 +47,10 @@ constexpr int kNumXcd = 8;
 // larger ones go through plan_kernel.
 constexpr int kDecPlanMaxSeqs = 1024;
 // Such a launch cuts each kv-head's list of pages into runs of at least kDecMinPages pages;
-// several kv-heads share a workgroup if its waves' shares hold kDecHeadPages pages or more.
+// several kv-heads share a workgroup if kDecPieceCost times the pieces of the longest sequence are
+// at most the pages of a wave's share (DecShares).
 constexpr int kDecMinPages = 16;
-constexpr int kDecHeadPages = 64;
+constexpr int kDecPieceCost = 8;
 // Up to 64 sequences of at most kDecWholePages pages more than a run are not cut if there is a
 // workgroup for every (sequence, kv-head) pair.
 constexpr int kDecWholePages = 28;

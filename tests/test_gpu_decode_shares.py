@@ -44,6 +44,44 @@ def _decode_append(case, max_kv):
     return out, lse
 
 
+FILL = 0x7f7f7f7f
+
+
+def _decode_append_partials(case, max_kv):
+    """decode_append in a workspace filled with a pattern: (partials left in it per kv-head, out, lse).
+    A partial is head_dim + 2 words for each q-head of the group; the header is in front of them and the
+    arrival counters behind."""
+    from paper_2609_35158_amd import binding as bd
+    B, H, G, d = case.batch, case.num_kv_heads, case.num_q_heads // case.num_kv_heads, case.head_dim
+    ctx = torch.from_numpy(case.ctx_lens.astype(np.int32)).cuda()
+    desc = bd.make_desc(case.block_table, ctx, None, B, 1, max_kv)
+    ws = torch.full((bd.workspace_bytes(case.num_q_heads, case.k_pool, desc),), FILL & 0xff, dtype=torch.uint8, device="cuda")
+    out, lse = pa.decode_append(case.q, case.k_new, case.v_new, case.k_pool, case.v_pool, case.block_table, ctx, max_kv,
+                                scale=case.scale, return_lse=True, workspace=ws)
+    torch.cuda.synchronize()
+    words = ws.view(torch.int32)
+    assert int(words[3]) == 0
+    written = int((words[64:-(-(-4 * B * H // 256) * 64)] != FILL).sum())
+    assert written % (H * G * (d + 2)) == 0
+    return written // (H * G * (d + 2)), out, lse
+
+
+def _partials(ctx, runs, shares):
+    """Partials per kv-head of a page list cut into runs of equal shares: one per run that holds pages of
+    a sequence, for every sequence in more than one run."""
+    end = np.cumsum(np.asarray(ctx) // 16 + 1)
+    share, more = divmod(int(end[-1]), runs * shares)
+    begin = np.array([shares * x * share + min(shares * x, more) for x in range(runs)])
+    first = np.searchsorted(begin, np.concatenate([[0], end[:-1]]), side="right")
+    last = np.searchsorted(begin, end - 1, side="right")
+    return int((last - first + 1)[last > first].sum())
+
+
+def _grid(d):
+    """Workgroups of the decode grid: one per compute unit, two at head_dim 64."""
+    return torch.cuda.get_device_properties(0).multi_processor_count * (2 if d == 64 else 1)
+
+
 @pytest.mark.parametrize("name", list(CASES))
 def test_shares_against_oracle(name):
     ctx, H, G, d = CASES[name]
@@ -61,18 +99,55 @@ def test_shares_against_oracle(name):
     assert torch.equal(out, again) and torch.equal(lse, lse2), "the same call differs"
 
 
-@pytest.mark.parametrize("H,G,d", [(8, 2, 128), (4, 8, 128), (8, 1, 64)])
-def test_several_heads_per_workgroup(H, G, d):
-    """Shares of 64 pages or more per wave: H kv-heads in a workgroup, 8 / H shares of each."""
-    say("case: decode shares, %d kv-heads per workgroup, d=%d" % (H, d))
-    B = 130
-    per_wave = 66 * (2 if d == 64 else 1)             # d = 64 runs two workgroups per compute unit
-    pages = per_wave * (8 // H) * 256 // B + 1
+# (kv-heads, G, head_dim, sequences, shortest and longest context, host bound; kv-heads per workgroup)
+HEAD_CASES = [
+    # shares long for their sequences: 8 / heads shares of several kv-heads, one block of them and more
+    (8, 2, 128, 130, 4000, 6000, 0, 8),
+    (4, 8, 128, 130, 2000, 6000, 0, 4),
+    (2, 4, 128, 256, 1000, 8000, 0, 2),
+    (6, 1, 128, 300, 400, 1200, 0, 2),
+    (10, 1, 128, 300, 400, 1200, 0, 2),
+    (12, 2, 128, 150, 400, 1200, 0, 4),
+    (24, 1, 128, 60, 400, 1200, 0, 8),
+    (40, 1, 64, 100, 200, 900, 32768, 8),
+    (64, 1, 128, 32, 400, 1600, 0, 8),
+    # head_dim 64 runs two workgroups per compute unit: 512 runs need that many partial slots
+    (4, 2, 64, 600, 1000, 1500, 0, 4),
+    (8, 1, 64, 130, 2000, 6200, 65536, 8),
+    (8, 1, 64, 130, 2000, 6200, 0, 1),
+    # the longest sequence in too many pieces
+    (8, 2, 128, 16, 2000, 30000, 0, 1),
+    (16, 1, 128, 8, 4000, 16000, 0, 1),
+    (8, 4, 128, 48, 2000, 6000, 0, 1),
+]
+
+
+@pytest.mark.parametrize("H,G,d,B,lo,hi,bound,heads", HEAD_CASES)
+def test_several_heads_per_workgroup(H, G, d, B, lo, hi, bound, heads):
+    """Workgroups of several kv-heads where their shares are long for the sequences, of one elsewhere
+    (seen by the partials they leave); sampled sequences against the oracle, the pools byte for byte.  Slots of a last page past the new token hold NaN, which no result may show."""
+    say("case: decode shares, H=%d G=%d d=%d, %d sequences" % (H, G, d, B))
     rng = np.random.default_rng(9)
-    ctx = rng.integers(8 * pages, 24 * pages, size=B)
-    case = workloads.build_case("heads", 78, H * G, H, d, ctx, np.ones(B, np.int64), device="cuda", sentinel_unused=False)
-    out, lse = _decode_append(case, int(case.kv_lens.max()))
-    seqs = [0, 1, 2, 37, 64, 65, 100, 128, 129]
+    ctx = rng.integers(lo, hi, size=B, endpoint=True)
+    ctx[0], ctx[-1] = hi, lo
+    case = workloads.build_case("heads", 78, H * G, H, d, ctx, np.ones(B, np.int64), device="cuda")
+    if bound:
+        case.block_table = torch.nn.functional.pad(case.block_table, (0, bound // 16 - case.block_table.shape[1]))
+    k, v = case.k_pool.clone(), case.v_pool.clone()
+    last = torch.from_numpy(ctx).cuda()
+    page = case.block_table.long().gather(1, (last // 16)[:, None])[:, 0]
+    k[page, :, last % 16], v[page, :, last % 16] = case.k_new, case.v_new
+    n, out, lse = _decode_append_partials(case, bound or int(case.kv_lens.max()))
+    runs = _grid(d) // (H // heads)
+    say("   partials per kv-head %d" % n)
+    if heads > 1:
+        assert n == _partials(ctx, runs, 8 // heads)
+    else:
+        assert n <= 2 * runs
+    same = lambda x, y: torch.equal(x.view(torch.int16), y.view(torch.int16))
+    assert same(case.k_pool, k) and same(case.v_pool, v)
+    assert torch.isfinite(out.float()).all() and torch.isfinite(lse).all()
+    seqs = sorted({0, 1, B // 4, B // 2, B - 2, B - 1} | {int(x) for x in rng.integers(0, B, size=3)})
     o, l = oracle_sampled(case, seqs)
     for b in seqs:
         assert_close(bits(out[b:b + 1]), o[b], lse[b:b + 1].cpu().numpy(), l[b], what="sequence %d" % b)
