@@ -1730,17 +1730,18 @@ __device__ __forceinline__ bool all_within(DecPlanLds& P, int B, int most, int l
 struct DecShares {
   int heads, n_runs, len, more;
   __device__ __forceinline__ DecShares(DecPlanLds& P, int pages, int most, const DecPlanArgs& d) {
-    const int len_heads = d.heads > 1 ? (int)((unsigned)pages / (unsigned)(kWaves / d.heads * d.runs_heads)) : 0;
-    const int longest = min(len_heads, 1 << 15) * min(len_heads, 1 << 15) / kDecPieceCost;   // at most
-    if (d.heads > 1 && (unsigned)pages <= (unsigned)longest * (unsigned long long)d.batch && all_within(P, d.batch, most, longest)) {
+    // which form and how many runs: any wave and workgroup finds the same, exact quotients are not needed
+    const int len_heads = min((int)((float)pages * d.inv_shares_heads), 1 << 15);
+    const int longest = len_heads * len_heads / kDecPieceCost;            // at most, for several heads
+    if (d.heads > 1 && (long long)longest * d.batch >= pages && all_within(P, d.batch, most, longest)) {
       heads = d.heads;
       n_runs = d.runs_heads;
     } else {
       heads = 1;
       // Long sequences in few pairs take somewhat longer runs, so that a pair is not merged from 100
       // pieces: three of 5-20K tokens on one kv-head 22.0 us a call with kDecMinPages alone, 19.4 so.
-      const int least = kDecMinPages + (int)((unsigned)pages / (64u * (unsigned)d.batch));
-      n_runs = max(1, min(d.runs_one, pages / least));
+      const int least = kDecMinPages + (int)((float)pages * d.inv_64_seqs);
+      n_runs = max(1, min(d.runs_one, (int)((float)pages * __builtin_amdgcn_rcpf((float)least))));
     }
     const int n = n_runs * subs();
     len = (int)((unsigned)pages / (unsigned)n);
@@ -1874,20 +1875,26 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 4 : 2) void decode_kernel(AttnA
     return;
   }
   DecShares sh(P, total_pages, most, d);
-  // A few sequences not much longer than a run: a workgroup per (sequence, kv-head) instead of equal
-  // runs, so that no pair is cut between workgroups (the acknowledged stores, the count-in and the
-  // merge take about as long as 3 more pages a wave; us a call with equal runs and so, 32 q-heads:
-  // 4 of 200-400 tokens at 2 kv-heads 14.1 and 11.8; 24 of 500-1000 at 8 21.1 and 19.2; but one of
-  // 770 at 4, 30 pages over its run, 11.6 and 13.0).
-  bool whole_pairs = false;
-  if (B <= 64 && B * H <= (int)gridDim.x && sh.heads == 1) {
-    const int i = min((int)threadIdx.x & 63, B - 1), most = total_pages / sh.n_runs + kDecWholePages;
-    whole_pairs = !__any(P.pre[i + 1] - P.pre[i] > most);
+  // Runs of whole sequences, as many sequences each (one, if the grid holds a workgroup for every
+  // (sequence, kv-head) pair), instead of equal runs, where no run gets much longer by it: then no pair
+  // is cut between workgroups, and the acknowledged stores, the count-in and the merge, which take
+  // about as long as 3 more pages a wave, fall away.  us a call with equal runs and so, 32 q-heads:
+  // 4 sequences of 200-400 tokens at 2 kv-heads 14.1 and 11.8; 24 of 500-1000 at 8 21.1 and 19.2; but
+  // one of 770 at 4, 30 pages over its run, 11.6 and 13.0.  It needs no partial slots: with short
+  // sequences the workspace holds one per sequence, which allows equal runs for half of them only.
+  auto whole_begin = [&](int run) { return run * d.whole_seqs + min(run, d.whole_more); };
+  // (up to 64 sequences every wave holds all lengths, and one that is too much by itself is seen there)
+  bool whole_runs = sh.heads == 1 && !(B <= 64 && __any((most - kDecWholePages) * sh.n_runs > total_pages));
+  if (whole_runs && (B > 64 || d.runs_whole < B)) {
+    bool over = false;
+#pragma unroll 1
+    for (int i = lane; i < d.runs_whole; i += 64) {
+      const int pages = P.pre[whole_begin(i + 1)] - P.pre[whole_begin(i)];
+      over |= (long long)(pages - kDecWholePages) * sh.n_runs > total_pages;
+    }
+    whole_runs = !__any(over);
   }
-  if (whole_pairs) {
-    sh.heads = 1;
-    sh.n_runs = B;
-  }
+  if (whole_runs) sh.n_runs = d.runs_whole;
   const int n_blk = H / sh.heads;                   // head blocks
   if ((int)blockIdx.x >= sh.n_runs * n_blk) return;
   // Run x of a head block is workgroup x n_blk + (block - x) mod n_blk: the blocks of a run start
@@ -1896,9 +1903,9 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 4 : 2) void decode_kernel(AttnA
   const int g0 = (blockIdx.x + x) % n_blk * sh.heads;
   const int sub = w / sh.heads, g = g0 + w % sh.heads;
   int run0, t0, n;                                  // the run's first entry; the wave's share
-  if (whole_pairs) {
-    run0 = uni(P.pre[x]);
-    const int len = uni(P.pre[x + 1]) - run0, q = len / NW, r = len % NW;
+  if (whole_runs) {
+    run0 = uni(P.pre[whole_begin(x)]);
+    const int len = uni(P.pre[whole_begin(x + 1)]) - run0, q = len / NW, r = len % NW;
     t0 = run0 + w * q + min(w, r);
     n = q + (w < r);
   } else {
@@ -2444,12 +2451,17 @@ void set_decode_runs(DecPlanArgs& d, int num_kv_heads, int grid) {
   // a run leaves at most two partials per head, the second ones also at most one per sequence
   const int cap = std::max(1, std::max(d.max_dec / 2, d.max_dec - d.batch));
   d.runs_one = std::min(grid / num_kv_heads, cap);
+  d.runs_whole = std::min(grid / num_kv_heads, d.batch);
+  d.whole_seqs = d.batch / d.runs_whole;
+  d.whole_more = d.batch % d.runs_whole;
   d.heads = std::min(num_kv_heads & -num_kv_heads, kWaves);
   d.runs_heads = grid / (num_kv_heads / d.heads);
   if (d.runs_heads > cap) {                         // not enough slots for a full grid of them
     d.heads = 1;
     d.runs_heads = 0;
   }
+  d.inv_shares_heads = d.heads > 1 ? 1.f / (float)(kWaves / d.heads * d.runs_heads) : 0.f;
+  d.inv_64_seqs = 1.f / (64.f * (float)d.batch);
 }
 
 hipError_t launch_decode_prologue(const AttnArgs& a, const DecPlanArgs& d, hipStream_t stream) {

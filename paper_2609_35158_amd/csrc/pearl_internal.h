@@ -51,8 +51,7 @@ constexpr int kDecPlanMaxSeqs = 1024;
 // at most the pages of a wave's share (DecShares).
 constexpr int kDecMinPages = 16;
 constexpr int kDecPieceCost = 8;
-// Up to 64 sequences of at most kDecWholePages pages more than a run are not cut if there is a
-// workgroup for every (sequence, kv-head) pair.
+// The runs hold whole sequences if that makes none longer than an equal run by more than this.
 constexpr int kDecWholePages = 28;
 
 enum Mode : int { kModePrefill = 0, kModeDecode = 1, kModeMixed = 2 };
@@ -151,8 +150,12 @@ struct DecPlanArgs {
   int max_kv_len;
   int max_dec;           // partial slots per kv-head in the workspace
   int runs_one;          // runs of a kv-head's page list with one kv-head per workgroup (at most)
+  int runs_whole;        // runs of whole sequences: whole_seqs each, the first whole_more one more
+  int whole_seqs, whole_more;
   int heads;             // kv-heads of a workgroup that holds several (a power of two; 1: never)
   int runs_heads;        // runs of the page list then
+  float inv_shares_heads;  // 1 / shares of the page list then
+  float inv_64_seqs;     // 1 / (64 batch)
 };
 
 WsLayout workspace_layout(int batch, int total_q, int max_kv_len, int num_q_heads,

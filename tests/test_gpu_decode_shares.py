@@ -1,7 +1,8 @@
 """The equal-share decode kernel where its cuts can go wrong: fewer pages than waves, pairs that end
 exactly at a share's or a workgroup's boundary, one pair cut by many workgroups, many pairs per
-share, a few short sequences that are not cut at all, kv-head counts that do not divide the grid, both plan forms (up to 64 sequences and more),
-and workgroups of several kv-heads.  Each case goes through pearl_attn_decode_append (pools compared
+share, runs of whole sequences (one each and several), kv-head counts that do not divide the grid,
+both plan forms (up to 64 sequences and more), and workgroups of several kv-heads.  The cut that a
+case took is seen by the partials it leaves in the workspace.  Each case goes through pearl_attn_decode_append (pools compared
 byte for byte) and against the oracle.  Many sequences here hold only a few keys, so single weights
 dominate their rows; the bound is the one gpu_helpers.peaked_bound derives for that from the bf16
 roundings of the weights and the output (half an ulp of o, plus 2^-8 of the largest |v|, plus 1e-4
@@ -17,22 +18,31 @@ from gpu_helpers import assert_close, bits, gpu_append, oracle_sampled, say
 
 pytestmark = pytest.mark.gpu
 
-# name: (contexts, kv-heads, G, head_dim)
+# name: (contexts, kv-heads, G, head_dim, whether the runs hold whole sequences)
 CASES = {
-    "one-page": ([0], 1, 1, 64),
-    "fewer-pages-than-waves": ([5, 16, 40], 1, 8, 128),
-    "one-page-each-3-heads": ([0, 15, 14], 3, 2, 128),
-    "65-sequences": ([(7 * i) % 50 for i in range(65)], 2, 4, 64),
-    "64-sequences": ([(11 * i) % 70 for i in range(64)], 5, 1, 128),
-    "cuts-at-pair-ends": ([16 * 16 - 1] * 48, 8, 4, 128),
-    "cuts-at-pair-ends-d64": ([16 * 8 - 1] * 64, 4, 8, 64),
-    "whole-pairs": ([300, 0, 17, 410, 1, 255, 256], 8, 4, 128),
-    "whole-pairs-d64": ([50 * i for i in range(20)], 3, 8, 64),
-    "one-too-long-for-whole-pairs": ([900, 100, 90], 2, 2, 128),
-    "one-long": ([30011], 2, 8, 128),
-    "long-beside-short": ([20000, 3, 17, 9000, 1], 4, 2, 64),
-    "many-pairs-per-share": ([(37 * i) % 90 for i in range(520)], 8, 1, 64),
-    "1024-sequences": ([(5 * i) % 33 for i in range(1024)], 3, 2, 64),
+    "one-page": ([0], 1, 1, 64, True),
+    "fewer-pages-than-waves": ([5, 16, 40], 1, 8, 128, True),
+    "one-page-each-3-heads": ([0, 15, 14], 3, 2, 128, True),
+    "65-sequences": ([(7 * i) % 50 for i in range(65)], 2, 4, 64, True),
+    "64-sequences": ([(11 * i) % 70 for i in range(64)], 5, 1, 128, True),
+    "cuts-at-pair-ends": ([16 * 16 - 1] * 48 + [16 * 64 - 1], 8, 4, 128, False),
+    "cuts-at-pair-ends-d64": ([16 * 8 - 1] * 64 + [16 * 64 - 1], 4, 8, 64, False),
+    "whole-pairs": ([300, 0, 17, 410, 1, 255, 256], 8, 4, 128, True),
+    "whole-pairs-d64": ([30 * i for i in range(20)], 3, 8, 64, True),
+    "one-too-long-for-whole-pairs": ([900, 100, 90], 2, 2, 128, False),
+    "one-long": ([30011], 2, 8, 128, False),
+    "long-beside-short": ([20000, 3, 17, 9000, 1], 4, 2, 64, False),
+    "many-pairs-per-share": ([(37 * i) % 90 for i in range(520)] + [2000], 8, 1, 64, False),
+    "1024-sequences": ([(5 * i) % 33 for i in range(1023)] + [3000], 3, 2, 64, False),
+    # more sequences than one wave plans, a workgroup each and several to a workgroup; as many or
+    # more of them than the workspace (one slot per sequence) allows equal runs for
+    "whole-130": ([20 + (13 * i) % 230 for i in range(130)], 1, 2, 128, True),
+    "whole-130-one-longer": ([20 + (13 * i) % 230 for i in range(129)] + [1500], 1, 2, 128, False),
+    "whole-700": ([(13 * i) % 200 for i in range(700)], 2, 1, 64, True),
+    "whole-2-per-run": ([16 + (5 * i) % 48 for i in range(64)], 8, 4, 128, True),
+    "whole-3-or-4-per-run": ([16 + (5 * i) % 48 for i in range(111)], 8, 1, 128, True),
+    "whole-equal-lengths": ([16 * 20 - 1] * 128, 4, 1, 128, True),
+    "whole-1024-sequences": ([(5 * i) % 33 for i in range(1024)], 3, 2, 64, True),
 }
 
 
@@ -82,15 +92,31 @@ def _grid(d):
     return torch.cuda.get_device_properties(0).multi_processor_count * (2 if d == 64 else 1)
 
 
+def _equal_runs(ctx, H, d):
+    """Equal runs of one kv-head: a workgroup each, at least 16 pages, and at most two partial slots of
+    the workspace each, or one more than one per sequence."""
+    pages = np.asarray(ctx) // 16 + 1
+    B, total, longest = len(ctx), int(pages.sum()), int(pages.max())
+    pps = min(512, -(-max(16, -(-B * H * longest // 4096)) // 16) * 16)
+    slots = B * -(-longest // pps)
+    return max(1, min(_grid(d) // H, max(1, slots // 2, slots - B), total // (16 + total // (64 * B))))
+
+
 @pytest.mark.parametrize("name", list(CASES))
 def test_shares_against_oracle(name):
-    ctx, H, G, d = CASES[name]
+    ctx, H, G, d, whole = CASES[name]
     say("case: decode shares %s" % name)
     case = workloads.build_case(name, 77, H * G, H, d, np.array(ctx), np.ones(len(ctx), np.int64), device="cuda",
                                 extra_pages=2)
     kr, vr = oracle.kv_append(bits(case.k_pool), bits(case.v_pool), bits(case.k_new), bits(case.v_new),
                               case.block_table.cpu().numpy(), case.ctx_lens, None)
-    out, lse = _decode_append(case, int(case.kv_lens.max()))
+    n, out, lse = _decode_append_partials(case, int(case.kv_lens.max()))
+    if whole:
+        assert n == 0
+    else:
+        # (the quotient that gives the runs is an approximate one)
+        runs = _equal_runs(ctx, H, d)
+        assert n in {_partials(ctx, r, 8) for r in (runs - 1, runs, runs + 1) if r > 0}
     assert np.array_equal(bits(case.k_pool), kr) and np.array_equal(bits(case.v_pool), vr)
     o, l = oracle.attention(bits(case.q), kr, vr, case.block_table.cpu().numpy(), case.ctx_lens, None, case.scale)
     assert_close(bits(out), o, lse.cpu().numpy(), l, what=name,
