@@ -1616,12 +1616,14 @@ __device__ __forceinline__ bool dec_seq(const AttnArgs& a, const DecPlanArgs& d,
 // the fence that orders its own stores before them.
 __device__ __forceinline__ int decode_plan(const AttnArgs& a, const DecPlanArgs& d, DecPlanLds& P, int& most) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, B = d.batch;
+  // inclusive sums over the wave: inside rows of 16 lanes, then the rows' last lanes onto the rows after
   auto wave_scan = [&](int v) {
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int u = __shfl_up(v, off);
-      if (lane >= off) v += u;
-    }
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);     // row_shr:1, 2, 4, 8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);     // row_bcast:15 to rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);     // row_bcast:31 to rows 2 and 3
     return v;
   };
   if (B <= 64) {
@@ -1636,7 +1638,7 @@ __device__ __forceinline__ int decode_plan(const AttnArgs& a, const DecPlanArgs&
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const int total = __shfl(incl, 63);
+    const int total = __builtin_amdgcn_readlane(incl, 63);
     most = pages;
     return __any(bad) ? -1 : total;
   }
