@@ -176,11 +176,10 @@ pearl_status run_attention(int mode, const pearl_kv_shape* s, const pearl_seq_de
   hipStream_t hs = reinterpret_cast<hipStream_t>(stream);
   char* w = static_cast<char*>(ws);
   // Decode batches up to kDecPlanMaxSeqs are planned inside the attention kernel, which also merges
-  // the splits, if the batch's pages fit 32 bits and the grid holds a workgroup per kv-head;
-  // everything else is planned by plan_kernel and merged by the merge kernels.
+  // the splits (the batch's pages fit 32 bits as its block table does); everything else is planned by
+  // plan_kernel and merged by the merge kernels.
   const int dec_grid = mode == kModeDecode ? decode_grid(s->head_dim) : 0;
-  const bool dec_in_kernel = q->batch <= kDecPlanMaxSeqs && s->num_kv_heads <= dec_grid &&
-                             (int64_t)q->batch * cdiv(q->max_kv_len, kPage) <= INT32_MAX;
+  const bool dec_in_kernel = mode == kModeDecode && q->batch <= kDecPlanMaxSeqs;
   hipError_t e = hipSuccess;
   if (k_new && !dec_in_kernel) {
     e = launch_kv_append(static_cast<const uint16_t*>(k_new), static_cast<const uint16_t*>(v_new),
@@ -235,7 +234,7 @@ pearl_status run_attention(int mode, const pearl_kv_shape* s, const pearl_seq_de
   e = record_before(hs);
   if (e != hipSuccess) return fail(PEARL_ERR_HIP, "timing event: %s", hipGetErrorString(e));
   if (dec_in_kernel) {
-    e = launch_decode(a, d, s->head_dim, dec_grid, hs);
+    e = launch_decode(a, d, s->head_dim, hs);
   } else {
     const int kinds = mode == kModePrefill ? 1 : (mode == kModeDecode ? 2 : 3);
     e = launch_attention(a, s->head_dim, kinds, max_items, (int)pl.lay.max_pre, hs);

@@ -1868,7 +1868,6 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 4 : 2) void decode_kernel(AttnA
   const int lane = threadIdx.x & 63, w = uni(threadIdx.x >> 6);
   const int gi = lane >> 4, hh = lane & 15;
   const int G = a.group, H = a.num_kv_heads, H_q = a.num_q_heads, B = d.batch;
-  const bool head_ok = hh < G;
 
   int most;
   const int total_pages = uni(decode_plan(a, d, P, most));
@@ -1897,13 +1896,17 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 4 : 2) void decode_kernel(AttnA
     whole_runs = !__any(over);
   }
   if (whole_runs) sh.n_runs = d.runs_whole;
-  const int n_blk = H / sh.heads;                   // head blocks
+  const int n_blk = (H + sh.heads - 1) / sh.heads;  // head blocks
   if ((int)blockIdx.x >= sh.n_runs * n_blk) return;
   // Run x of a head block is workgroup x n_blk + (block - x) mod n_blk: the blocks of a run start
   // together, and every XCD (workgroup mod 8) sees all of them.
   const int x = blockIdx.x / n_blk;
-  const int g0 = (blockIdx.x + x) % n_blk * sh.heads;
-  const int sub = w / sh.heads, g = g0 + w % sh.heads;
+  // The last block overlaps the one before if the kv-heads don't divide: the waves of its first `dup`
+  // kv-heads read along, so that all keep pace, and leave no results.
+  const int blk0 = (blockIdx.x + x) % n_blk * sh.heads;
+  const int g0 = min(blk0, H - sh.heads), dup = blk0 - g0;
+  const int sub = w / sh.heads, j_w = w % sh.heads, g = g0 + j_w;
+  const bool head_ok = hh < G && j_w >= dup;
   int run0, t0, n;                                  // the run's first entry; the wave's share
   if (whole_runs) {
     run0 = uni(P.pre[whole_begin(x)]);
@@ -2029,7 +2032,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 4 : 2) void decode_kernel(AttnA
         const bool is_v = lane >= PT::CPR;
         const u32x4 y = *reinterpret_cast<const u32x4*>(
             st + buf + (is_v ? PT::TBYTES + r * PT::ROWB + ((c ^ PT::vswz(r)) << 4) : PT::koff(r, c)));
-        if (lane < 2 * PT::CPR && raw_cur >= 0 && raw_cur < a.num_pages) {
+        if (lane < 2 * PT::CPR && j_w >= dup && raw_cur >= 0 && raw_cur < a.num_pages) {
           const size_t dst = (((size_t)raw_cur * H + g) * kPage + r) * D + 8 * c;
           *reinterpret_cast<u32x4*>((is_v ? a.v_pool_w : a.k_pool_w) + dst) = y;
         }
@@ -2126,7 +2129,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 4 : 2) void decode_kernel(AttnA
       const int pu = uni(P.pre[b]);                 // the pair's first entry
       const int second = pu > run0;
       const int slot2 = per_pair ? sh.n_runs + b : 2 * x + 1;   // the run's second slot
-      for (int t = threadIdx.x; t < rows * (D / 2); t += kThreads) {
+      for (int t = threadIdx.x + dup * G * (D / 2); t < rows * (D / 2); t += kThreads) {
         const int r = t / (D / 2), dim = 2 * (t - r * (D / 2));
         const int j = r / G, head = r - j * G;      // kv-head of the workgroup, q-head of the group
         float M = -INFINITY, L = 0.f, o0 = 0.f, o1 = 0.f;
@@ -2171,7 +2174,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 4 : 2) void decode_kernel(AttnA
     const int j = task >> 1;
     const CutPair c = s_cut[task & 1];
     int last = 0;
-    if (c.b >= 0) {
+    if (c.b >= 0 && j >= dup) {
       const int ctr = per_pair ? (g0 + j) * B + c.b : (g0 + j) * sh.n_runs + c.x0;
       last = __hip_atomic_fetch_add(&a.split_cnt[ctr], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == c.n - 1;
     }
@@ -2452,18 +2455,28 @@ int decode_grid(int head_dim) {
 void set_decode_runs(DecPlanArgs& d, int num_kv_heads, int grid) {
   // a run leaves at most two partials per head, the second ones also at most one per sequence
   const int cap = std::max(1, std::max(d.max_dec / 2, d.max_dec - d.batch));
-  d.runs_one = std::min(grid / num_kv_heads, cap);
-  d.runs_whole = std::min(grid / num_kv_heads, d.batch);
+  // a workgroup per run if they are all resident; with more kv-heads than that, runs for several rounds
+  const int per_head = std::max(1, (num_kv_heads <= grid ? grid : kDecRounds * grid) / num_kv_heads);
+  d.runs_one = std::min(per_head, cap);
+  d.runs_whole = std::min(per_head, d.batch);
   d.whole_seqs = d.batch / d.runs_whole;
   d.whole_more = d.batch % d.runs_whole;
   d.heads = std::min(num_kv_heads & -num_kv_heads, kWaves);
-  d.runs_heads = grid / (num_kv_heads / d.heads);
-  if (d.runs_heads > cap) {                         // not enough slots for a full grid of them
+  // Above 64 kv-heads, where adjacent reads matter most, blocks of 8 with a partial last one (us a call
+  // with a kv-head per workgroup and so, of 400-1600 tokens: 8 sequences at 255 kv-heads 193 and 173, 15
+  // at 129 181 and 168, 28 at 71 176 and 166; but 40 at 31 103 and 106).
+  if (d.heads < 4 && num_kv_heads > 64) d.heads = kWaves;
+  const int blocks = (num_kv_heads + d.heads - 1) / d.heads;
+  d.runs_heads = std::max(1, grid / blocks);
+  if (8 * cap >= 7 * d.runs_heads) {                // not enough slots for a full grid of them, nearly
+    d.runs_heads = std::min(d.runs_heads, cap);
+  } else {
     d.heads = 1;
     d.runs_heads = 0;
   }
   d.inv_shares_heads = d.heads > 1 ? 1.f / (float)(kWaves / d.heads * d.runs_heads) : 0.f;
   d.inv_64_seqs = 1.f / (64.f * (float)d.batch);
+  d.grid = std::max(grid, std::max(std::max(d.runs_one, d.runs_whole) * num_kv_heads, d.runs_heads * blocks));
 }
 
 hipError_t launch_decode_prologue(const AttnArgs& a, const DecPlanArgs& d, hipStream_t stream) {
@@ -2473,11 +2486,11 @@ hipError_t launch_decode_prologue(const AttnArgs& a, const DecPlanArgs& d, hipSt
   return hipGetLastError();
 }
 
-hipError_t launch_decode(const AttnArgs& a, const DecPlanArgs& d, int head_dim, int grid, hipStream_t stream) {
+hipError_t launch_decode(const AttnArgs& a, const DecPlanArgs& d, int head_dim, hipStream_t stream) {
   if (head_dim == 64)
-    hipLaunchKernelGGL(decode_kernel<64>, dim3((unsigned)grid), dim3(kThreads), 0, stream, a, d);
+    hipLaunchKernelGGL(decode_kernel<64>, dim3((unsigned)d.grid), dim3(kThreads), 0, stream, a, d);
   else
-    hipLaunchKernelGGL(decode_kernel<128>, dim3((unsigned)grid), dim3(kThreads), 0, stream, a, d);
+    hipLaunchKernelGGL(decode_kernel<128>, dim3((unsigned)d.grid), dim3(kThreads), 0, stream, a, d);
   return hipGetLastError();
 }
 

@@ -51,6 +51,8 @@ constexpr int kDecPlanMaxSeqs = 1024;
 // at most the pages of a wave's share (DecShares).
 constexpr int kDecMinPages = 16;
 constexpr int kDecPieceCost = 8;
+// With more kv-heads than resident workgroups, runs for about this many rounds of them.
+constexpr int kDecRounds = 4;
 // The runs hold whole sequences if that makes none longer than an equal run by more than this.
 constexpr int kDecWholePages = 28;
 
@@ -156,6 +158,7 @@ struct DecPlanArgs {
   int runs_heads;        // runs of the page list then
   float inv_shares_heads;  // 1 / shares of the page list then
   float inv_64_seqs;     // 1 / (64 batch)
+  int grid;              // workgroups of the launch
 };
 
 WsLayout workspace_layout(int batch, int total_q, int max_kv_len, int num_q_heads,
@@ -193,12 +196,12 @@ hipError_t launch_attention(const AttnArgs& a, int head_dim, int kinds, int64_t 
 hipError_t launch_merge(const AttnArgs& a, int head_dim, int batch, hipStream_t stream);
 
 // Decode planned in-kernel (batch <= kDecPlanMaxSeqs): the zeroing prologue, then the kernel.
-// grid: workgroups of a full grid (decode_grid), all resident.
+// Workgroups that are resident together.
 int decode_grid(int head_dim);
-// Sets d's run counts for such a grid (num_kv_heads <= grid), from d.batch and d.max_dec.
+// Sets d's run counts and grid for so many resident workgroups, from d.batch and d.max_dec.
 void set_decode_runs(DecPlanArgs& d, int num_kv_heads, int grid);
 hipError_t launch_decode_prologue(const AttnArgs& a, const DecPlanArgs& d, hipStream_t stream);
-hipError_t launch_decode(const AttnArgs& a, const DecPlanArgs& d, int head_dim, int grid, hipStream_t stream);
+hipError_t launch_decode(const AttnArgs& a, const DecPlanArgs& d, int head_dim, hipStream_t stream);
 
 // Merge of split prefill tiles; jobs_cap bounds the device-side job count.
 hipError_t launch_merge_prefill(const AttnArgs& a, int head_dim, int64_t jobs_cap, hipStream_t stream);

@@ -42,6 +42,10 @@ CASES = {
     "whole-2-per-run": ([16 + (5 * i) % 48 for i in range(64)], 8, 4, 128, True),
     "whole-3-or-4-per-run": ([16 + (5 * i) % 48 for i in range(111)], 8, 1, 128, True),
     "whole-equal-lengths": ([16 * 20 - 1] * 128, 4, 1, 128, True),
+    # more kv-heads than workgroups at a time
+    "300-heads": ([40, 0, 100], 300, 1, 128, True),
+    "300-heads-cut": ([3000], 300, 1, 128, False),
+    "513-heads-d64": ([1500, 20], 513, 1, 64, False),
     "whole-1024-sequences": ([(5 * i) % 33 for i in range(1024)], 3, 2, 64, True),
 }
 
@@ -92,14 +96,19 @@ def _grid(d):
     return torch.cuda.get_device_properties(0).multi_processor_count * (2 if d == 64 else 1)
 
 
-def _equal_runs(ctx, H, d):
-    """Equal runs of one kv-head: a workgroup each, at least 16 pages, and at most two partial slots of
-    the workspace each, or one more than one per sequence."""
-    pages = np.asarray(ctx) // 16 + 1
-    B, total, longest = len(ctx), int(pages.sum()), int(pages.max())
+def _slot_runs(ctx, H, bound=0):
+    """Runs that the workspace's partial slots allow: two slots each, or one more than one per sequence."""
+    B, longest = len(ctx), max(int(np.max(ctx)) // 16 + 1, bound // 16)
     pps = min(512, -(-max(16, -(-B * H * longest // 4096)) // 16) * 16)
     slots = B * -(-longest // pps)
-    return max(1, min(_grid(d) // H, max(1, slots // 2, slots - B), total // (16 + total // (64 * B))))
+    return max(1, slots // 2, slots - B)
+
+
+def _equal_runs(ctx, H, d):
+    """Equal runs of one kv-head: a workgroup each, of at least 16 pages, as many as there are slots for."""
+    total = int((np.asarray(ctx) // 16 + 1).sum())
+    per_head = max(1, (_grid(d) if H <= _grid(d) else 4 * _grid(d)) // H)
+    return max(1, min(per_head, _slot_runs(ctx, H), total // (16 + total // (64 * len(ctx)))))
 
 
 @pytest.mark.parametrize("name", list(CASES))
@@ -137,6 +146,13 @@ HEAD_CASES = [
     (24, 1, 128, 60, 400, 1200, 0, 8),
     (40, 1, 64, 100, 200, 900, 32768, 8),
     (64, 1, 128, 32, 400, 1600, 0, 8),
+    # a last block of 8 kv-heads that overlaps the one before by 1, 7 and 5 of them
+    (71, 1, 128, 28, 400, 1200, 0, 8),
+    (129, 1, 64, 30, 500, 900, 32768, 8),
+    (83, 2, 128, 20, 500, 900, 32768, 8),
+    # more kv-heads than workgroups at a time
+    (300, 1, 128, 6, 400, 1600, 0, 4),
+    (257, 1, 128, 7, 400, 1600, 0, 8),
     # head_dim 64 runs two workgroups per compute unit: 512 runs need that many partial slots
     (4, 2, 64, 600, 1000, 1500, 0, 4),
     (8, 1, 64, 130, 2000, 6200, 65536, 8),
@@ -164,7 +180,7 @@ def test_several_heads_per_workgroup(H, G, d, B, lo, hi, bound, heads):
     page = case.block_table.long().gather(1, (last // 16)[:, None])[:, 0]
     k[page, :, last % 16], v[page, :, last % 16] = case.k_new, case.v_new
     n, out, lse = _decode_append_partials(case, bound or int(case.kv_lens.max()))
-    runs = _grid(d) // (H // heads)
+    runs = min(max(1, _grid(d) // -(-H // heads)), _slot_runs(ctx, H, bound))
     say("   partials per kv-head %d" % n)
     if heads > 1:
         assert n == _partials(ctx, runs, 8 // heads)
