@@ -64,6 +64,29 @@ def gpu_attend(case: workloads.Case, mode: str, return_lse: bool = True, max_kv_
     raise ValueError(mode)
 
 
+def decode_with_partials(case: workloads.Case, max_kv_len: int, append: bool = True):
+    """decode_append (or decode) in a workspace filled with a pattern: (partials it leaves there per
+    kv-head, out, lse).  A partial is head_dim + 2 words for each q-head of the group; the header is in
+    front of them and the arrival counters are behind.  Batches that the decode kernel plans itself only."""
+    from paper_2609_35158_amd import binding as bd
+    B, H, G, d = case.batch, case.num_kv_heads, case.num_q_heads // case.num_kv_heads, case.head_dim
+    assert B <= 1024
+    fill = 0x7f7f7f7f
+    ctx, _ = dev_lengths(case)
+    desc = bd.make_desc(case.block_table, ctx, None, B, 1, max_kv_len)
+    ws = torch.full((bd.workspace_bytes(case.num_q_heads, case.k_pool, desc) // 4,), fill, dtype=torch.int32, device="cuda")
+    new = (case.k_new, case.v_new) if append else ()
+    fn = pa.decode_append if append else pa.decode
+    out, lse = fn(case.q, *new, case.k_pool, case.v_pool, case.block_table, ctx, max_kv_len, scale=case.scale,
+                  return_lse=True, workspace=ws.view(torch.uint8))
+    torch.cuda.synchronize()
+    assert int(ws[3]) == 0
+    counters = (4 * B * H + 255) // 256 * 64
+    written = int((ws[64:ws.numel() - counters] != fill).sum())
+    assert written % (H * G * (d + 2)) == 0
+    return written // (H * G * (d + 2)), out, lse
+
+
 def oracle_full(case: workloads.Case, k_pool_bits=None, v_pool_bits=None):
     kp = bits(case.k_pool) if k_pool_bits is None else k_pool_bits
     vp = bits(case.v_pool) if v_pool_bits is None else v_pool_bits

@@ -14,7 +14,7 @@ import torch
 import oracle
 import paper_2609_35158_amd as pa
 from paper_2609_35158_amd import workloads
-from gpu_helpers import assert_close, bits, gpu_append, oracle_sampled, say
+from gpu_helpers import assert_close, bits, decode_with_partials, gpu_append, oracle_sampled, say
 
 pytestmark = pytest.mark.gpu
 
@@ -58,28 +58,6 @@ def _decode_append(case, max_kv):
     return out, lse
 
 
-FILL = 0x7f7f7f7f
-
-
-def _decode_append_partials(case, max_kv):
-    """decode_append in a workspace filled with a pattern: (partials left in it per kv-head, out, lse).
-    A partial is head_dim + 2 words for each q-head of the group; the header is in front of them and the
-    arrival counters behind."""
-    from paper_2609_35158_amd import binding as bd
-    B, H, G, d = case.batch, case.num_kv_heads, case.num_q_heads // case.num_kv_heads, case.head_dim
-    ctx = torch.from_numpy(case.ctx_lens.astype(np.int32)).cuda()
-    desc = bd.make_desc(case.block_table, ctx, None, B, 1, max_kv)
-    ws = torch.full((bd.workspace_bytes(case.num_q_heads, case.k_pool, desc),), FILL & 0xff, dtype=torch.uint8, device="cuda")
-    out, lse = pa.decode_append(case.q, case.k_new, case.v_new, case.k_pool, case.v_pool, case.block_table, ctx, max_kv,
-                                scale=case.scale, return_lse=True, workspace=ws)
-    torch.cuda.synchronize()
-    words = ws.view(torch.int32)
-    assert int(words[3]) == 0
-    written = int((words[64:-(-(-4 * B * H // 256) * 64)] != FILL).sum())
-    assert written % (H * G * (d + 2)) == 0
-    return written // (H * G * (d + 2)), out, lse
-
-
 def _partials(ctx, runs, shares):
     """Partials per kv-head of a page list cut into runs of equal shares: one per run that holds pages of
     a sequence, for every sequence in more than one run."""
@@ -119,7 +97,7 @@ def test_shares_against_oracle(name):
                                 extra_pages=2)
     kr, vr = oracle.kv_append(bits(case.k_pool), bits(case.v_pool), bits(case.k_new), bits(case.v_new),
                               case.block_table.cpu().numpy(), case.ctx_lens, None)
-    n, out, lse = _decode_append_partials(case, int(case.kv_lens.max()))
+    n, out, lse = decode_with_partials(case, int(case.kv_lens.max()))
     if whole:
         assert n == 0
     else:
@@ -179,7 +157,7 @@ def test_several_heads_per_workgroup(H, G, d, B, lo, hi, bound, heads):
     last = torch.from_numpy(ctx).cuda()
     page = case.block_table.long().gather(1, (last // 16)[:, None])[:, 0]
     k[page, :, last % 16], v[page, :, last % 16] = case.k_new, case.v_new
-    n, out, lse = _decode_append_partials(case, bound or int(case.kv_lens.max()))
+    n, out, lse = decode_with_partials(case, bound or int(case.kv_lens.max()))
     runs = min(max(1, _grid(d) // -(-H // heads)), _slot_runs(ctx, H, bound))
     say("   partials per kv-head %d" % n)
     if heads > 1:

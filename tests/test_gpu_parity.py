@@ -11,7 +11,7 @@ import torch
 import oracle
 import paper_2609_35158_amd as pa
 from paper_2609_35158_amd import workloads
-from gpu_helpers import (assert_close, bits, bounds, dev_lengths, gpu_append, gpu_attend, oracle_full,
+from gpu_helpers import (assert_close, bits, bounds, decode_with_partials, dev_lengths, gpu_append, gpu_attend, oracle_full,
                          say)
 
 pytestmark = pytest.mark.gpu
@@ -104,9 +104,10 @@ def test_random_small_decode(seed):
 
 @pytest.mark.parametrize("batch", [1, 63, 64, 65])
 def test_decode_planner_boundary(batch):
-    """Decode batches of at most 64 sequences are planned by one wave, larger ones by all 8 waves;
-    both lists must cover every split exactly once.  Contexts give several full splits per
-    sequence and short last splits of many sizes (and one sequence of a single key)."""
+    """Decode batches of at most 64 sequences are planned by every wave alone, larger ones by all 8
+    waves together; both page lists must cover every page exactly once.  Contexts of many lengths
+    give pairs inside one wave's share, pairs cut by shares and by workgroups, and one sequence of a
+    single key."""
     rng = np.random.default_rng(9100 + batch)
     ctx = rng.integers(0, 2600, size=batch, endpoint=True)
     ctx[0] = 0
@@ -122,24 +123,49 @@ def test_decode_planner_boundary(batch):
 
 
 def test_split_plans_agree():
-    """The same decode with different split plans (a larger max_kv_len bound gives larger splits)
-    agrees within tolerance; the same plan twice is bit-identical."""
+    """The same sequences decoded under different cuts agree within tolerance, the same cut twice is
+    bit-identical.  Larger max_kv_len bounds leave the cut of a batch as it is (the shares follow from
+    the lengths) and only change where its partials lie; other sequences in the batch, another order
+    or a batch of its own cut a sequence elsewhere, seen by the number of partials that the launches
+    leave and by the last bits of the longest sequence's fp32 LSE."""
     say("case: split plans")
     ctx = np.array([20000, 7000, 15, 1, 33000])
-    case = workloads.build_case("splits", 77, 32, 4, 128, ctx, np.ones(5, np.int64), device="cuda")
+    case = workloads.build_case("splits", 77, 32, 4, 128, np.concatenate([ctx, np.full(100, 250)]),
+                                np.ones(105, np.int64), device="cuda")
     kr, vr = _append_and_check(case)
-    o_ref, l_ref = oracle_full(case, kr, vr)
     # widen the block table so the larger host bounds stay legal (extra columns are never read)
     bt = case.block_table
     case.block_table = torch.cat([bt, torch.zeros(bt.shape[0], 2000000 // 16 - bt.shape[1],
                                                   dtype=bt.dtype, device=bt.device)], 1).contiguous()
+
+    def sub(seqs):
+        return workloads.Case(name="sub", seed=0, num_q_heads=32, num_kv_heads=4, head_dim=128, ctx_lens=case.ctx_lens[seqs],
+                              q_lens=case.q_lens[seqs], block_table=case.block_table[seqs].contiguous(), k_pool=case.k_pool,
+                              v_pool=case.v_pool, k_new=None, v_new=None, q=case.q[seqs].contiguous(), scale=case.scale)
+
+    five = sub([0, 1, 2, 3, 4])
+    o_ref, l_ref = oracle_full(five, kr, vr)
     outs = []
     for bound in (33001, 33001, 200000, 2000000):
-        out, lse = gpu_attend(case, "decode", max_kv_len=bound)
+        out, lse = gpu_attend(five, "decode", max_kv_len=bound)
         torch.cuda.synchronize()
         assert_close(bits(out), o_ref, lse.cpu().numpy(), l_ref, what="bound %d" % bound)
         outs.append(bits(out))
     assert np.array_equal(outs[0], outs[1])
+    cuts = {"alone": [0, 1, 2, 3, 4], "reversed": [4, 3, 2, 1, 0], "beside 60": list(range(65)),
+            "behind 100": list(range(5, 105)) + [0, 1, 2, 3, 4], "two of them": [1, 3], "one": [4], "a short one": [2]}
+    left, longest = {}, {}
+    for what, seqs in cuts.items():
+        part = sub(seqs)
+        left[what], out, lse = decode_with_partials(part, 33001, append=False)
+        say("   %s: %d partials per kv-head" % (what, left[what]))
+        rows = [i for i, b in enumerate(seqs) if b < 5]
+        ref = [seqs[i] for i in rows]
+        assert_close(bits(out)[rows], o_ref[ref], lse.cpu().numpy()[rows], l_ref[ref], what=what)
+        if 4 in seqs:
+            longest[what] = lse[seqs.index(4)].cpu().numpy().tobytes()
+    say("   %d different cuts of the longest sequence" % len(set(longest.values())))
+    assert left["a short one"] == 0 and len(set(left.values())) >= 4 and len(set(longest.values())) >= 4, "the cuts are meant to differ"
 
 
 def test_page_permutation_bit_identical():
@@ -403,9 +429,8 @@ def test_prefill_key_splits_long_context_sampled():
 
 def test_batches_larger_than_one_planner_chunk():
     """More sequences than one pass of the planners' threads: the block scans carry offsets from
-    one chunk of sequences to the next.  Decode of 800 sequences long enough for several full
-    splits each is planned inside the attention kernel (512 sequences per chunk), so its full
-    splits, short last splits and their size classes span chunks; decode of 1500 sequences (above
+    one chunk of sequences to the next.  Decode of 800 sequences is planned inside the attention
+    kernel (512 sequences per chunk), so its page list and shares span chunks; decode of 1500 sequences (above
     the in-kernel limit) and a mixed batch of 1100 sequences with ragged chunks go through the
     planner kernel (256 sequences per chunk)."""
     say("case: 800-sequence decode with multi-split sequences")
@@ -442,8 +467,7 @@ def test_batches_larger_than_one_planner_chunk():
 
 def test_prefill_tile_order_spans_chunks():
     """Prefill of 300 sequences with up to 4 tiles each and no key splits: tiles are written by
-    size class across the whole launch, a sequence's run of tiles in one class claimed together,
-    and the classes and runs span the planner's 256-sequence chunks.  Every row's LSE (preset to
+    size class across the whole launch, and the classes span the planner's 256-sequence chunks.  Every row's LSE (preset to
     NaN) must be written, and sampled sequences match the oracle."""
     from gpu_helpers import oracle_sampled
     from paper_2609_35158_amd import binding as bd

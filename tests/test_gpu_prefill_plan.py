@@ -1,7 +1,7 @@
 """The planner's prefill entries where they can go wrong: key splits of tiles of very different
 lengths in one sequence (short tiles have fewer splits), sequences with and without splits in one
-launch, as many entries as one thread keeps and more, several chunks of sequences, and launches
-that never split.  Every row's LSE (preset to NaN) must be written; rows are compared with the
+launch, as many entries as one thread keeps and more, several chunks of sequences (with key splits
+and without), and launches that never split; the header says whether tiles were split.  Every row's LSE (preset to NaN) must be written; rows are compared with the
 oracle within the bf16 tolerance (1e-2 max, 1e-3 mean), rows of few keys within
 gpu_helpers.peaked_bound."""
 import numpy as np
@@ -15,21 +15,31 @@ from gpu_helpers import assert_close, bits, bounds, dev_lengths, gpu_append, ora
 
 pytestmark = pytest.mark.gpu
 
-# name: (contexts, new tokens, kv-heads, G, head_dim, sequences checked)
+# name: (contexts, new tokens, kv-heads, G, head_dim, sequences checked, whether prefill and mixed launches split tiles)
 CASES = {
-    "one-prompt-split": ([0], [1700], 2, 2, 64, [0]),
-    "prompt-beside-long-context": ([0, 9000, 40], [900, 70, 3], 2, 4, 128, [0, 1, 2]),
-    "equal-tiles-split": ([6000, 6010], [256, 250], 4, 8, 128, [0, 1]),
-    "no-split-below-1024-keys": ([700, 0, 300], [300, 1000, 1], 1, 1, 64, [0, 1, 2]),
-    "more-entries-than-kept": ([(13 * i) % 50 for i in range(200)], [180] * 200, 1, 8, 64, [0, 7, 99, 199]),
-    "two-chunks": ([(29 * i) % 400 for i in range(260)], [1 + (7 * i) % 90 for i in range(260)], 2, 4, 64, [0, 255, 256, 259]),
+    "one-prompt-split": ([0], [1700], 2, 2, 64, [0], (True, True)),
+    "prompt-beside-long-context": ([0, 9000, 40], [900, 70, 3], 2, 4, 128, [0, 1, 2], (True, True)),
+    "equal-tiles-split": ([6000, 6010], [256, 250], 4, 8, 128, [0, 1], (True, True)),
+    "no-split-below-1024-keys": ([700, 0, 300], [300, 1000, 1], 1, 1, 64, [0, 1, 2], (False, False)),
+    "more-entries-than-kept": ([(13 * i) % 50 for i in range(200)], [180] * 200, 1, 8, 64, [0, 7, 99, 199], (False, False)),
+    "two-chunks": ([(29 * i) % 400 for i in range(260)], [1 + (7 * i) % 90 for i in range(260)], 2, 4, 64, [0, 255, 256, 259],
+                   (False, False)),
+    # key splits where the planner goes over its sequences twice, more than 256 of them, with split tiles
+    # in the first chunk and in the second; and as many splits as there are slots for
+    "two-chunks-split": ([8000 if i in (3, 250, 258) else (29 * i) % 50 for i in range(262)], [1 + (7 * i) % 90 for i in range(262)],
+                         1, 2, 128, [0, 3, 250, 255, 256, 258, 261], (True, False)),
+    "chunks-beside-300-decodes": ([6500 if i == 100 else 9000 if i == 280 else (31 * i) % 400 for i in range(302)],
+                                  [100 if i in (100, 280) else 1 for i in range(302)], 4, 8, 128, [0, 99, 100, 255, 256, 280, 301],
+                                  (False, True)),
+    "many-splits": ([5, 9000, 9100], [130, 500, 480], 1, 8, 64, [0, 1, 2], (True, True)),
 }
 
 
 @pytest.mark.parametrize("mode", ["prefill", "mixed"])
 @pytest.mark.parametrize("name", list(CASES))
 def test_prefill_entries(name, mode):
-    ctx, ql, H, G, d, seqs = CASES[name]
+    from paper_2609_35158_amd import binding as bd
+    ctx, ql, H, G, d, seqs, splits = CASES[name]
     say("case: prefill plan %s (%s)" % (name, mode))
     case = workloads.build_case(name, 91, H * G, H, d, np.array(ctx), np.array(ql), device="cuda", extra_pages=1)
     gpu_append(case)
@@ -37,9 +47,15 @@ def test_prefill_entries(name, mode):
     max_q, max_kv = bounds(case)
     lse = torch.full((case.total_q, case.num_q_heads), float("nan"), dtype=torch.float32, device="cuda")
     fn = {"prefill": pa.prefill_append, "mixed": pa.mixed}[mode]
+    desc = bd.make_desc(case.block_table, dctx, cu, case.total_q, max_q, max_kv)
+    ws = torch.empty(bd.workspace_bytes(case.num_q_heads, case.k_pool, desc), dtype=torch.uint8, device="cuda")
     out, lse = fn(case.q, case.k_pool, case.v_pool, case.block_table, dctx, cu, max_q, max_kv, scale=case.scale,
-                  return_lse=True, lse=lse)
+                  return_lse=True, lse=lse, workspace=ws)
     torch.cuda.synchronize()
+    hdr = ws[:64 * 4].view(torch.int32).cpu().numpy()
+    say("   entries %d, keys per split %d, split tiles %d" % (hdr[1], hdr[5], hdr[6]))
+    assert hdr[3] == 0
+    assert (hdr[5] > 0 and hdr[6] > 0) if splits[mode == "mixed"] else (hdr[5] == 0 and hdr[6] == 0)
     assert torch.isfinite(lse).all(), "rows left unwritten"
     rng = np.random.default_rng(3)
     toks = {b: tile_edge_tokens(ql[b], 256 // G, 8, rng) for b in seqs}
