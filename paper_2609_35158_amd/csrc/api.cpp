@@ -294,8 +294,9 @@ WsLayout workspace_layout(int batch, int total_q, int max_kv_len, int num_q_head
   const int T = kRowsPerTile / group;
   // prefill tiles: sum_b ceil(n_b / T) <= total_q / T + batch, and <= total_q
   const int64_t tiles = std::min<int64_t>(total_q, total_q / T + batch);
-  // split prefill items: every tile splits into at most ceil(max_kv_len / kMinSplitKeys) ranges,
-  // and the planner keeps the split items of a launch within kMaxPreSplitItems
+  // split prefill items: slots for every tile in ranges of kMinSplitKeys keys, at most
+  // kMaxPreSplitItems.  The planner takes finer cuts (from about half its candidate's size) where
+  // their items fit these slots, and coarser ones or whole tiles where they don't.
   l.pre_slots = 0;
   if (has_prefill && max_kv_len > kMinSplitKeys)
     l.pre_slots = std::min<int64_t>(kMaxPreSplitItems, (int64_t)num_kv_heads * tiles * cdiv(max_kv_len, kMinSplitKeys));

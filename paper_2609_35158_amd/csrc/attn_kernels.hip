@@ -1578,10 +1578,11 @@ __global__ __launch_bounds__((KernelCfg<D, kKinds>::NT)) void attn_kernel(AttnAr
 // store acknowledgement, the count-in and the last merge (5-8 us).  Before, splits of equal size
 // came from a work queue and each drained its pipeline and merged 8 waves (3.6 us per split, and a
 // tail of a split's length).  Times of a call, before and now (32 q-heads, d = 128 unless said;
-// same card, in turn): 64 sequences of 2K-16K tokens, 8 kv-heads 361 -> 352 us; 256 around 6K
-// tokens, 4 kv-heads 647 -> 634; 512 of 64-1024 tokens 202 -> 190; 32 around 6K, 4 kv-heads
-// 93.1 -> 82.7; 48 of 500-6000 tokens, 16 q-heads, 8 kv-heads, d = 64 60.9 -> 55.1; one of 2731
-// tokens 14.6 -> 13.2, of 16000 34.1 -> 21.5; 200 of 40-160 tokens 37.4 -> 26.4.
+// same card, in turn): 64 sequences of 2K-16K tokens, 8 kv-heads 362 -> 352 us; 256 around 6K
+// tokens, 4 kv-heads 647 -> 632 (both 2-4% over batches of other such lengths); 512 of 64-1024 tokens
+// 202 -> 190; 32 around 6K, 4 kv-heads 93.4 -> 82.8; 48 of 500-6000 tokens, 16 q-heads, 8 kv-heads,
+// d = 64 60.8 -> 55.5; one of 2731 tokens 14.6 -> 13.2, of 16000 34.0 -> 21.4; 200 of 40-160 tokens
+// 37.5 -> 24.8.
 // The shares follow from the lengths alone, so results do not depend on timing.  Every workgroup
 // finds its place by itself from the prefix sums of the pages per sequence (decode_plan), so the
 // call is a zeroing launch and this kernel.
@@ -2265,7 +2266,9 @@ __global__ __launch_bounds__(256) void merge_kernel(AttnArgs a, int batch) {
 // Merge of split prefill tiles, grid-stride over the (job, kv-head, tile row) the planner recorded:
 // D / 4 lanes per row, 4 dims each, kPreMergeBlock splits in flight at a time.  Same combination as
 // the decode merge, over the tile's splits.  It reads 4 D bytes per row and split once; few loads in
-// flight per row, so several rows share a wave.
+// flight per row, so several rows share a wave.  2, 4 and 8 splits in flight are within 2% of a call
+// (append, plan, attention, merge): eight turns of 64-300 tokens on 4-8K contexts 183 / 183 / 186 us, 16
+// of 100-300 on 4-6K at d = 64 129 / 130 / 131.
 // ------------------------------------------------------------------------------------------------
 constexpr int kMergeMaxBlocks = 2048;
 constexpr int kPreMergeBlock = 4;

@@ -29,9 +29,9 @@ constexpr int kDecLongSplitPages = 128;
 // workspace size a pure function of the shapes; the launch grid uses the device's real count.
 constexpr int kPlanComputeUnits = 256;
 // Prefill tiles are split along the keys only when the launch has few of them (the rule is at
-// plan_kernel); a split is aimed at kMinSplitKeys / 2 keys or more, the workspace is sized for
-// kMinSplitKeys, and all split items of a launch fit in kMaxPreSplitItems partial slots
-// (kRowsPerTile rows each).
+// plan_kernel).  The workspace is sized for splits of kMinSplitKeys keys; finer ones are taken where
+// they fit, down to equal parts of at most kMinSplitKeys / 2 keys (about half of that at the least).
+// All split items of a launch fit in kMaxPreSplitItems partial slots (kRowsPerTile rows each).
 constexpr int kMinSplitKeys = 1024;
 constexpr int kMaxPreSplitItems = 2 * kPlanComputeUnits;
 // Prefill launches split tiles only up to this many tile items (tile x kv-head).
