@@ -1903,11 +1903,12 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 4 : 2) void decode_kernel(AttnA
   // together, and every XCD (workgroup mod 8) sees all of them.
   const int x = blockIdx.x / n_blk;
   // The last block overlaps the one before if the kv-heads don't divide: the waves of its first `dup`
-  // kv-heads read along, so that all keep pace, and leave no results.
+  // kv-heads go along, so that all keep pace, but read one page again and again and leave no results.
   const int blk0 = (blockIdx.x + x) % n_blk * sh.heads;
   const int g0 = min(blk0, H - sh.heads), dup = blk0 - g0;
   const int sub = w / sh.heads, j_w = w % sh.heads, g = g0 + j_w;
   const bool head_ok = hh < G && j_w >= dup;
+  const int pages_seen = j_w < dup ? 1 : a.num_pages;
   int run0, t0, n;                                  // the run's first entry; the wave's share
   if (whole_runs) {
     run0 = uni(P.pre[whole_begin(x)]);
@@ -1951,7 +1952,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 4 : 2) void decode_kernel(AttnA
     // a page's copies: a sequence's last page may hold the new row and rows past the end; every other
     // one is two whole blocks
     auto issue_page = [&](const PageCursor& c, int raw, char* dst) {
-      const int phys = clamp_page(raw, a.num_pages);
+      const int phys = clamp_page(raw, pages_seen);
       if (c.p == c.np - 1) {
         NewRow nr{-1, 0, a.k_pool, a.v_pool};       // no new row (valid pointers, never selected)
         if (a.k_new) {
