@@ -1213,10 +1213,11 @@ __device__ __forceinline__ void issue_whole_or_last(const AttnArgs& a, int phys,
 
 // Attends the G heads to logical page p staged at buf, updating the wave's online softmax state.
 // kFine: the weights enter P.V as two bf16 parts, the upper 8 significant bits (cut off, so the rest
-// is >= 0) and the rest, side by side in the k dimension of one 16x16x32 product (the keys twice).
+// is >= 0) and the rest, in a product each on the same V operand (side by side in one 16x16x32
+// product the operand had to be copied, which cost calls 0.1-0.4 us).
 // Rounded to bf16 once, a weight is off by up to 2^-9 unless it is the largest of its run, which is
 // exactly 1: the fewer runs a sequence is cut into, the larger the error, and the equal shares'
-// long runs took the error of 64 sequences of 2K-16K tokens from 0.00179 to 0.00187 (2-norm, against
+// long runs took the error of 64 sequences of 2K-16K tokens from 0.00177 to 0.00185 (2-norm, against
 // 64 bits); in two parts it is 0.00166, that of rounding the exact result to bf16.
 template <int D, bool kFine>
 __device__ __forceinline__ void decode_consume(int p, int kv, const bf16x8* qop, f32x4* oacc, float& m_run,
@@ -1266,13 +1267,15 @@ __device__ __forceinline__ void decode_consume(int p, int kv, const bf16x8* qop,
   // O^T += V^T P^T: the transposing read gives lane l dim 16 mb + l % 16 of keys 4 gi .. 4 gi + 3,
   // the k index of the P^T operand that lane already holds
   const int r0 = 4 * gi + (j >> 2);
+  i16x4 v[PT::MB];
 #pragma unroll
   for (int mb = 0; mb < PT::MB; ++mb) {
-    const i16x4 v = lds_read_tr(buf, PT::voff(r0, 16 * mb + 4 * (j & 3)));
-    if constexpr (kFine)
-      oacc[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(concat_tr(v, v), concat_tr(pop, rest), oacc[mb], 0, 0, 0);
-    else
-      oacc[mb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(v, pop, oacc[mb], 0, 0, 0);
+    v[mb] = lds_read_tr(buf, PT::voff(r0, 16 * mb + 4 * (j & 3)));
+    oacc[mb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(v[mb], pop, oacc[mb], 0, 0, 0);
+  }
+  if constexpr (kFine) {
+#pragma unroll
+    for (int mb = 0; mb < PT::MB; ++mb) oacc[mb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(v[mb], rest, oacc[mb], 0, 0, 0);
   }
 }
 
