@@ -1885,8 +1885,11 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 4 : 2) void decode_kernel(AttnA
   // is cut between workgroups, and the acknowledged stores, the count-in and the merge, which take
   // about as long as 3 more pages a wave, fall away.  us a call with equal runs and so, 32 q-heads:
   // 4 sequences of 200-400 tokens at 2 kv-heads 14.1 and 11.8; 24 of 500-1000 at 8 21.1 and 19.2; but
-  // one of 770 at 4, 30 pages over its run, 11.6 and 13.0.  It needs no partial slots: with short
-  // sequences the workspace holds one per sequence, which allows equal runs for half of them only.
+  // one of 770 at 4, 30 pages over its run, 11.6 and 13.0; two sequences a run, 64 of 16-64 at 8 16.0 and
+  // 11.1.  The line at 28 pages more than an equal run, against 12 and 60: 32 of 200-700 at 8 16.4 / 18.6 /
+  // 16.4, 128 of 100-400 at 8 30.1 / 32.1 / 30.2, 300 of 100-500 at 2 25.2 / 25.2 / 26.2, 24 of 500-1200
+  // at 8 22.0 / 22.1 / 21.1.  It needs no partial slots: with short sequences the workspace holds one
+  // per sequence, which allows equal runs for half of them only.
   auto whole_begin = [&](int run) { return run * d.whole_seqs + min(run, d.whole_more); };
   // (up to 64 sequences every wave holds all lengths, and one that is too much by itself is seen there)
   bool whole_runs = sh.heads == 1 && !(B <= 64 && __any((most - kDecWholePages) * sh.n_runs > total_pages));
